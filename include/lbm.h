@@ -251,9 +251,10 @@ lbm_status stg_inlet_fill_noalloc(lbm_handle h, const lbm_stg* stg, double t);
  * pull-stream / boundary / wall-model / MRT-Smagorinsky collision runs over
  * all nodes, on the handle's stream.  With LBM_STORE_F16DEV the blocks away
  * from the inlet, outlet and statistics planes (wall rows included) run in a
- * lean kernel after a general kernel for the other blocks (one fused launch on
- * lattices of up to 2^24 nodes); with LBM_STORE_F32 the general kernel covers
- * all blocks, one dispatch per range of x-planes (lbm_collide_dispatches).
+ * lean kernel, one dispatch per range of x-planes, after a general kernel for
+ * the other blocks (one fused launch on lattices of up to 2^24 nodes); with
+ * LBM_STORE_F32 the general kernel covers all blocks, one dispatch per range of
+ * x-planes (lbm_collide_dispatches).
  * stg: bound when non-NULL; required (now or earlier) with LBM_X_INFLOW.
  * Asynchronous on the handle's stream.
  */
@@ -383,8 +384,8 @@ const char* lbm_status_str(lbm_status s);
 /* When enabled, every launch of the dominant collide-stream kernel (with
    LBM_STORE_F32 the general kernel over all nodes, one launch being the
    step's dispatches over its x-chunks (lbm_collide_dispatches); with
-   LBM_STORE_F16DEV the bulk kernel over the nodes away from the inlet, outlet
-   and statistics planes, or on lattices of up to 2^24 nodes the one kernel
+   LBM_STORE_F16DEV the bulk kernel's dispatches over the nodes away from the
+   inlet, outlet and statistics planes, or on lattices of up to 2^24 nodes the one kernel
    over all nodes) is bracketed by HIP events on the handle's stream;
    *total_ms and *launches report the summed kernel time since the last
    reset, and *nodes_per_launch the nodes one launch updates (reading

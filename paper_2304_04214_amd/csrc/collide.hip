@@ -842,9 +842,9 @@ hipError_t launch_wall_line(lbm_ctx* h, CollideArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// The bulk kernel variant for the storage, the body force and the FP16
-// reference offsets.
-void launch_bulk_kernel(lbm_ctx* h, const CollideArgs& a, bool f16, hipStream_t stream) {
+// The bulk blocks of one step (FP16 storage; none with FP32): the kernel
+// variant for the body force and the reference offsets.
+void launch_bulk_kernel(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
   const int n = h->n_int;
   const int* bl = h->d_blist_int;
   if (h->fused) {
@@ -864,22 +864,22 @@ void launch_bulk_kernel(lbm_ctx* h, const CollideArgs& a, bool f16, hipStream_t 
     }
     return;
   }
-  if (n == 0) return;
-  if (!f16) {
-    if (a.has_g)
-      collide_bulk_kernel<false, true, false><<<n, BLOCK, 0, stream>>>(a, bl, a.dref, a.dpull);
-    else
-      collide_bulk_kernel<false, false, false><<<n, BLOCK, 0, stream>>>(a, bl, a.dref, a.dpull);
-  } else if (a.dref) {
-    if (a.has_g)
-      collide_bulk_kernel<true, true, true><<<n, BLOCK, 0, stream>>>(a, bl, a.dref, a.dpull);
-    else
-      collide_bulk_kernel<true, false, true><<<n, BLOCK, 0, stream>>>(a, bl, a.dref, a.dpull);
-  } else {
-    if (a.has_g)
-      collide_bulk_kernel<true, true, false><<<n, BLOCK, 0, stream>>>(a, bl, a.dref, a.dpull);
-    else
-      collide_bulk_kernel<true, false, false><<<n, BLOCK, 0, stream>>>(a, bl, a.dref, a.dpull);
+  // one dispatch per x-chunk of the list (see CHUNK_BLOCKS_F16)
+  for (size_t k = 0; k + 1 < h->int_off.size(); ++k) {
+    const int m = h->int_off[k + 1] - h->int_off[k];
+    const int* bk = bl + h->int_off[k];
+    if (m <= 0) continue;
+    if (a.dref) {
+      if (a.has_g)
+        collide_bulk_kernel<true, true, true><<<m, BLOCK, 0, stream>>>(a, bk, a.dref, a.dpull);
+      else
+        collide_bulk_kernel<true, false, true><<<m, BLOCK, 0, stream>>>(a, bk, a.dref, a.dpull);
+    } else {
+      if (a.has_g)
+        collide_bulk_kernel<true, true, false><<<m, BLOCK, 0, stream>>>(a, bk, a.dref, a.dpull);
+      else
+        collide_bulk_kernel<true, false, false><<<m, BLOCK, 0, stream>>>(a, bk, a.dref, a.dpull);
+    }
   }
 }
 
@@ -926,11 +926,10 @@ hipError_t launch_step_explicit(lbm_ctx* h, const void* src, void* dst, const fl
   a.u_in = u_in;
   a.stats_on = 0;
   a.wall_acc = nullptr;
-  const bool f16 = h->cfg.storage == LBM_STORE_F16DEV;
   hipError_t e = launch_wall_line(h, a, stream);
   if (e != hipSuccess) return e;
   if (!h->fused) launch_edge_kernels(h, a, stream);
-  launch_bulk_kernel(h, a, f16, stream);
+  launch_bulk_kernel(h, a, stream);
   return hipGetLastError();
 }
 
@@ -944,7 +943,7 @@ hipError_t launch_bulk(lbm_ctx* h, int src, int dst, hipStream_t stream, const f
   if (u_in) a.u_in = u_in;
   if (h->cfg.wall_avg == LBM_WALL_AVG_LINE && h->cfg.wall_model && h->cfg.ywall != LBM_Y_PERIODIC)
     a.wall_line = h->d_wall_line;
-  launch_bulk_kernel(h, a, h->cfg.storage == LBM_STORE_F16DEV, stream);
+  launch_bulk_kernel(h, a, stream);
   return hipGetLastError();
 }
 
@@ -981,8 +980,9 @@ std::vector<int> xcd_order(const std::vector<int>& entries, int zc, const std::v
 // round FP16 deviations differently (the bulk kernel computes on deviations),
 // and a recompute with statistics off must reproduce the forward run.
 // With FP32 storage the boundary list (all blocks) is cut into x-chunks of
-// about CHUNK_BLOCKS blocks, each ordered by xcd_order on its own, since
-// every chunk is a dispatch of its own.
+// about CHUNK_BLOCKS blocks, with FP16 storage the bulk list into chunks of
+// about CHUNK_BLOCKS_F16 (unless it is part of a fused launch), each ordered by
+// xcd_order on its own, since every chunk is a dispatch of its own.
 hipError_t build_block_lists(lbm_ctx* h, const std::vector<int>& plane_of_x) {
   const lbm_config& c = h->cfg;
   std::vector<int> in, bd;
@@ -1009,26 +1009,34 @@ hipError_t build_block_lists(lbm_ctx* h, const std::vector<int>& plane_of_x) {
       }
     }
   }
-  in = xcd_order(in, h->zc, &in_heavy);
-  // bd is in memory order (x-major), so an x-range is a contiguous run of it
-  int nchunk = 1;
-  if (!split) nchunk = (int)std::max<int64_t>(1, std::llround((double)h->nblocks / CHUNK_BLOCKS));
-  const int planes = (c.nx + std::min(nchunk, c.nx) - 1) / std::min(nchunk, c.nx);
+  // Cut a list in memory order (x-major: an x-range is a contiguous run of it)
+  // into ranges of `planes` planes, each ordered for the XCDs.
   const int per_plane = h->zc * h->yg;
-  {
+  auto chunk = [&](std::vector<int>& v, int planes, const std::vector<char>* heavy, std::vector<int>& off) {
     std::vector<int> out;
-    h->bnd_off.assign(1, 0);
+    off.assign(1, 0);
     size_t i = 0;
     for (int x0 = 0; x0 < c.nx; x0 += planes) {
       std::vector<int> part;
-      while (i < bd.size() && bd[i] / per_plane < x0 + planes) part.push_back(bd[i++]);
+      std::vector<char> hv;
+      while (i < v.size() && v[i] / per_plane < x0 + planes) {
+        if (heavy && i % h->zc == 0) hv.push_back((*heavy)[i / h->zc]);
+        part.push_back(v[i++]);
+      }
       if (part.empty()) continue;
-      part = xcd_order(part, h->zc);
+      part = xcd_order(part, h->zc, heavy ? &hv : nullptr);
       out.insert(out.end(), part.begin(), part.end());
-      h->bnd_off.push_back((int)out.size());
+      off.push_back((int)out.size());
     }
-    bd.swap(out);
-  }
+    v.swap(out);
+  };
+  auto chunk_planes = [&](int blocks) {
+    const int n = (int)std::min<int64_t>(c.nx, std::max<int64_t>(1, std::llround((double)h->nblocks / blocks)));
+    return (c.nx + n - 1) / n;
+  };
+  const int planes = split ? c.nx : chunk_planes(CHUNK_BLOCKS);
+  chunk(bd, planes, nullptr, h->bnd_off);
+  chunk(in, h->fused ? c.nx : chunk_planes(CHUNK_BLOCKS_F16), &in_heavy, h->int_off);
   h->chunk_planes = planes;
   hipError_t err;
   for (int k = 0; k < 2; ++k) {

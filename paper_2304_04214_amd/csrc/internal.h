@@ -28,6 +28,11 @@ constexpr int64_t FUSED_MAX_NODES = int64_t(1) << 24;  // FP16: one fused collid
 // dispatch over all blocks reaches 0.69-0.70; the FP16 bulk kernel gains
 // nothing from it and keeps one dispatch.
 constexpr int CHUNK_BLOCKS = 30000;
+// FP16 storage: the bulk kernel's blocks likewise, in dispatches of about this
+// many.  1536x128x384, us per step where one dispatch takes 980: 384 planes
+// (74,000 blocks) 934, 192 planes 950, 128 planes 968, 64 planes 1032; on a second
+// MI355X, by this constant: 50,000 949, 74,000 953, 100,000 961, 150,000 977.
+constexpr int CHUNK_BLOCKS_F16 = 60000;
 // FP32 state buffers together larger than this: non-temporal population
 // stores (the 256 MB Infinity Cache cannot hold the state from one step to
 // the next).
@@ -122,6 +127,7 @@ struct lbm_ctx {
   // Offsets of the x-chunks of d_blist_bnd (chunks + 1 entries; one chunk
   // except with FP32 storage on large lattices), and the x-planes per chunk.
   std::vector<int> bnd_off;
+  std::vector<int> int_off;  // the same of d_blist_int
   int chunk_planes = 0;
   int64_t int_nodes = 0;  // nodes updated by one bulk launch
   // FP16 storage: boundary blocks in the general kernel, then the bulk blocks
