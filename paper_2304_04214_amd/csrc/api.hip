@@ -186,6 +186,7 @@ lbm_status lbm_create(const lbm_config* cfg, void* f_a, void* f_b, float* hist_a
   h->zc = (cfg->nz + lbm::ZT - 1) / lbm::ZT;
   h->yg = (cfg->ny + lbm::YROWS - 1) / lbm::YROWS;
   h->split = cfg->storage == LBM_STORE_F16DEV;
+  lbm::plan_rows(h);
   h->fused = h->split && h->N <= lbm::FUSED_MAX_NODES;
   const int64_t nb = (int64_t)cfg->nx * h->yg * h->zc;
   if (nb >= (int64_t(1) << 31)) {

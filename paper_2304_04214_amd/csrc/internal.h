@@ -136,6 +136,9 @@ struct lbm_ctx {
   // launch over all blocks.
   bool split = false;
   bool fused = false;
+  // Lattices of few spanwise nodes: rows per block of the row kernel (rows.hip;
+  // 0: not used), its threads and its blocks per plane.
+  int rows = 0, row_threads = 0, row_groups = 0;
   double* d_stats = nullptr;
   double* d_wall_acc = nullptr;  // [2][nx][zc], with the wall model
   float* d_wall_line = nullptr;  // [2][nx] line-averaged u_tau of the current step
@@ -185,6 +188,9 @@ hipError_t launch_wall_line(lbm_ctx* h, CollideArgs& a, hipStream_t stream);
 std::vector<int> xcd_order(const std::vector<int>& entries, int zc, const std::vector<char>* heavy = nullptr);
 hipError_t launch_field_export(lbm_ctx* h, const float* bricks, float* soa);
 hipError_t launch_field_import(lbm_ctx* h, const float* soa, float* bricks);
+// rows.hip
+void plan_rows(lbm_ctx* h);
+hipError_t launch_rows(lbm_ctx* h, const CollideArgs& a, hipStream_t stream);
 // adjoint.hip
 hipError_t launch_adjoint(lbm_ctx* h, const AdjointArgs& args, int storage_f16, double t_next, bool fill_inlet,
                           float* u_in, float* fluct);

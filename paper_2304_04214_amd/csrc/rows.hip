@@ -1,0 +1,228 @@
+// The collide-stream step on lattices of few spanwise nodes, FP32 storage
+// (Algorithm 1 as in collide.hip's general kernel, with the same arithmetic:
+// the states are equal bit for bit).
+//
+// The kernels of collide.hip give every row (x, y) of 64 spanwise nodes a wave,
+// so with nz <= 32 half the lanes or more hold no node (three quarters at
+// nz = 16).  Here a block takes whole rows of one x-plane, as many as its
+// threads hold, and a thread the node t % nz of row t / nz: the row is a
+// per-lane value, the plane a scalar.  Bound by the latency of one round of
+// blocks on small lattices, on large ones by the 128-byte lines of the padded
+// bricks, of which nz = 16 uses half.  Per step, general kernel -> this one:
+// 200x20x16 8.2 -> 6.5 us, 64x32x32 7.3 -> 6.3, 400x40x32 18.5 -> 15.3,
+// 880x80x16 60 -> 56.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "collide.h"
+#include "internal.h"
+#include "stream.h"
+
+namespace lbm {
+namespace {
+
+constexpr int MAXT = 256, MAXZ = 32;  // threads of a block, spanwise nodes
+
+struct RowsLds {
+  float u2[2][2][MAXZ];  // (u_x, u_z) of the rows next to the walls
+  float ut[2][MAXZ];     // u_tau of the wall rows
+  float u[3][MAXT];      // velocities of a sampled plane
+};
+
+// Sum over a wave; the order of the reductions in collide.hip.
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, ZT);
+  return v;
+}
+
+// rb rows of one x-plane a block, `groups` blocks a plane.  NT: non-temporal
+// population stores.
+template <bool NT>
+__global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int rb, int groups,
+                                                            const int* __restrict__ plane_of_x) {
+  __shared__ RowsLds L;
+  const int gy = blockIdx.x % groups, xq = blockIdx.x / groups;
+  const int x = xq == 0 ? a.nx - 1 : xq - 1;  // the end planes, whose nodes have more to do, go first
+  const bool inflow = a.xbc == LBM_X_INFLOW, walls = a.ywall != LBM_Y_PERIODIC;
+  const bool bb = a.ywall == LBM_Y_BOUNCEBACK;
+  const bool outlet = inflow && x == a.nx - 1, inlet = inflow && x == 0;
+  const int t = threadIdx.x;
+  const int row = t / a.nz, z = t - row * a.nz;
+  const int base = min(rb * gy, a.ny - rb);
+  const bool valid = row < rb;  // threads without a node compute another one and store nothing
+  const int y = valid ? base + row : base;
+  const bool mine = valid && y >= rb * gy;  // rows shared with the previous group are helpers only
+
+  // ---- pulls (the wall rules of issue_pulls): plane by c_x (scalar), row and column by lane ----
+  const Geo gx = make_geo(a, x, 0);
+  const int zs[3] = {z == a.nz - 1 ? 0 : z + 1, z, z == 0 ? a.nz - 1 : z - 1};  // source z for c_z = -1, 0, 1
+  const bool bot = walls && y == 0, top = walls && y == a.ny - 1;
+  uint32_t srow[3], scol[3];
+#pragma unroll
+  for (int c = -1; c <= 1; ++c) {
+    int ys = y - c;
+    ys = ys < 0 ? ys + a.ny : (ys >= a.ny ? ys - a.ny : ys);
+    if (c == 1 ? bot : (c == -1 && top)) ys = y;
+    srow[c + 1] = (uint32_t)ys * (BRICK * 4u);
+    scol[c + 1] = (uint32_t)zs[c + 1] * 4u;
+  }
+  const char* s0 = static_cast<const char*>(a.src);
+  const size_t plane = (size_t)a.ny * BRICK * 4u;  // bytes per x-plane (one z-chunk)
+  const uint32_t self = srow[1] + scol[1];
+  auto out = [&](int i) { return CY[i] == 1 ? bot : (CY[i] == -1 && top); };
+  // population i as the node of plane xn pulls it, xsrc = xn - c_x: beyond a
+  // wall the mirrored one of the own row, or the opposite one of the own node
+  auto pull = [&](int xn, int xsrc, int i) {
+    const bool own = CY[i] != 0 && bb && out(i);
+    const int m = out(i) ? (bb ? opp(i) : REFLY[i]) : i;
+    const char* p = s0 + (size_t)xsrc * plane;
+    if (CY[i] != 0 && bb) p = own ? s0 + (size_t)xn * plane : p;
+    return *reinterpret_cast<const float*>(p + ((own ? self : srow[CY[i] + 1] + scol[CZ[i] + 1]) + (uint32_t)m * (ZT * 4u)));
+  };
+  float f[Q];
+#pragma unroll
+  for (int i = 0; i < Q; ++i) f[i] = pull(x, gx.xs[CX[i] + 1], i);
+#pragma unroll
+  for (int i = 0; i < Q; ++i)
+    if (CX[i] != 0) f[i] = gx.xok[CX[i] + 1] || (CY[i] != 0 && bb && out(i)) ? f[i] : 0.f;
+
+  // ---- outlet and inlet (x_rules) ----
+  if (outlet) {
+    const Geo g2 = make_geo(a, x - 1, 0);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      const int i = OUT5[k];
+      const int hidx = (k * a.ny + y) * a.nz + z;
+      const float v = __builtin_fmaf(a.out_wh, a.hist_in[hidx], a.out_wu * pull(x - 1, g2.xs[CX[i] + 1], i));
+      f[i] = v;
+      if (mine) a.hist_out[hidx] = v;
+    }
+  }
+  if (inlet) inlet_regularize(a, y, z, f);
+
+  // ---- density, momentum, forces, collision (node_update) ----
+  float rho = 0.f, jx = 0.f, jy = 0.f, jz = 0.f;
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    rho += f[i];
+    if (CX[i]) jx += CX[i] * f[i];
+    if (CY[i]) jy += CY[i] * f[i];
+    if (CZ[i]) jz += CZ[i] * f[i];
+  }
+  float Fx = 0.f, Fy = 0.f, Fz = 0.f;
+  if (a.has_g) {
+    Fx = rho * a.g[0];
+    Fy = rho * a.g[1];
+    Fz = rho * a.g[2];
+  }
+  const bool wblock = a.wall_model && (base == 0 || base == a.ny - rb);  // block-uniform
+  const bool wrow = a.wall_model && (bot || top);
+  if (wblock) {  // the block holds a wall row and its neighbour
+    const float ir = 1.f / rho;
+    if (valid && base == 0 && y == 1) {
+      L.u2[0][0][z] = jx * ir;
+      L.u2[0][1][z] = jz * ir;
+    }
+    if (valid && base == a.ny - rb && y == a.ny - 2) {
+      L.u2[1][0][z] = jx * ir;
+      L.u2[1][1][z] = jz * ir;
+    }
+    __syncthreads();
+    if (wrow) {
+      const int w = bot ? 0 : 1;
+      float fwx, fwz, ut;
+      wall_force(a, rho, jx * ir, jz * ir, L.u2[w][0][z], L.u2[w][1][z], fwx, fwz, ut, w, x);
+      Fx += fwx;
+      Fz += fwz;
+      if (mine) L.ut[w][z] = ut;
+    }
+  }
+  float ux, uy, uz;
+  const Tau0 t0 = tau0_of_x(a, x);
+  const Pairs pr = make_pairs(f);
+  if (a.has_g || wrow)
+    collide<true>(a, t0, f, pr, rho, jx, jy, jz, Fx, Fy, Fz, ux, uy, uz);
+  else
+    collide<false>(a, t0, f, pr, rho, jx, jy, jz, 0.f, 0.f, 0.f, ux, uy, uz);
+  if (valid && !(rho > 0.f && rho < 1e30f)) atomicOr(a.err, ERRBIT_NONFINITE);
+  if (mine) {
+    char* d = static_cast<char*>(a.dst) + (size_t)x * plane;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) Pop<false>::stp<NT>(d + i * (ZT * 4), i, self, f[i], 0.f);
+  }
+
+  // ---- statistics: sums over z (nz <= 32, so one wave holds a row) of the block's own rows ----
+  const int lane = t & (ZT - 1), wave = uni(t >> 6), nw = blockDim.x / ZT;
+  const bool on = lane < a.nz;
+  if (a.stats_on) {
+    const int p = plane_of_x[x];
+    if (p >= 0) {  // block-uniform
+      L.u[0][t] = ux;
+      L.u[1][t] = uy;
+      L.u[2][t] = uz;
+      __syncthreads();
+      for (int q = rb * gy - base + wave; q < rb; q += nw) {
+        const int k0 = q * a.nz + (on ? lane : 0);
+        const double dx = L.u[0][k0], dy = L.u[1][k0], dz = L.u[2][k0];
+        const double v[9] = {dx, dy, dz, dx * dx, dy * dy, dz * dz, dx * dy, dx * dz, dy * dz};
+        double* s = a.stats + ((size_t)p * a.ny + base + q) * 9;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+          const double sum = wave_sum(on ? v[k] : 0.0);
+          if (lane == 0) s[k] += sum;
+        }
+      }
+    }
+  }
+  if (wblock && a.wall_acc) {  // block-uniform: sums of u_tau, by the blocks that own a wall row
+    __syncthreads();
+    for (int w = wave; w < 2; w += nw) {
+      if (w == 0 ? gy != 0 : gy != groups - 1) continue;
+      const double sum = wave_sum(on ? (double)L.ut[w][lane] : 0.0);
+      if (lane == 0) a.wall_acc[(size_t)w * a.nx + x] += sum;
+    }
+  }
+}
+
+}  // namespace
+
+// Rows per block and blocks per plane of the row kernel (0 rows: not used).
+// FP32 storage with nz <= 32: beyond that a row's segments no longer begin on
+// 64-byte borders of the waves' accesses and the kernel loses (500x150x36 155
+// -> 166-197 us per step, 300x90x85 76 -> 78-87).  The rows are those that
+// leave the fewest threads without a row of their own.  Up to 2^17 nodes the
+// chip takes all blocks in one round and the smallest such blocks are taken
+// (200x20x16: 6.5 us per step with one wave a block, 7.4 with two of which a
+// quarter idles); above, the largest of up to 256 threads (400x40x32 15.3 us,
+// 16.9 with 128).  Every block has at least two rows, a wall row and the row
+// next to it.
+void plan_rows(lbm_ctx* h) {
+  const lbm_config& c = h->cfg;
+  h->rows = 0;
+  if (c.storage != LBM_STORE_F32 || c.nz > MAXZ) return;
+  const bool small = h->N <= (int64_t(1) << 17);
+  const int most = std::min((small ? MAXT / 2 : MAXT) / c.nz, c.ny);
+  int64_t least = 0;  // threads of a plane
+  for (int k = 2; k <= most; ++k) {
+    const int rb = small ? k : most + 2 - k;
+    const int threads = (rb * c.nz + ZT - 1) / ZT * ZT, groups = (c.ny + rb - 1) / rb;
+    if (h->rows && (int64_t)threads * groups >= least) continue;
+    least = (int64_t)threads * groups;
+    h->rows = rb;
+    h->row_threads = threads;
+    h->row_groups = groups;
+  }
+}
+
+hipError_t launch_rows(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
+  const dim3 grid((unsigned)h->cfg.nx * h->row_groups), block(h->row_threads);
+  if (a.nt_store)
+    collide_rows_kernel<true><<<grid, block, 0, stream>>>(a, h->rows, h->row_groups, a.plane_of_x);
+  else
+    collide_rows_kernel<false><<<grid, block, 0, stream>>>(a, h->rows, h->row_groups, a.plane_of_x);
+  return hipGetLastError();
+}
+
+}  // namespace lbm
