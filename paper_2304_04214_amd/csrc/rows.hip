@@ -81,6 +81,22 @@ __global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int r
     if (CY[i] != 0 && bb) p = own ? s0 + (size_t)xn * plane : p;
     return *reinterpret_cast<const float*>(p + ((own ? self : srow[CY[i] + 1] + scol[CZ[i] + 1]) + (uint32_t)m * (ZT * 4u)));
   };
+  // What the end planes read besides the pulls is loaded with them: their nodes
+  // are the launch's longest, and the loads' latency would come on top.
+  const int pz = y * a.nz + z;
+  float e0[5], e1[5];
+  if (outlet) {
+    const Geo g2 = make_geo(a, x - 1, 0);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      e0[k] = a.hist_in[k * a.ny * a.nz + pz];
+      e1[k] = pull(x - 1, g2.xs[CX[OUT5[k]] + 1], OUT5[k]);
+    }
+  }
+  if (inlet) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) e0[k] = a.u_in[k * a.ny * a.nz + pz];
+  }
   float f[Q];
 #pragma unroll
   for (int i = 0; i < Q; ++i) f[i] = pull(x, gx.xs[CX[i] + 1], i);
@@ -90,17 +106,14 @@ __global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int r
 
   // ---- outlet and inlet (x_rules) ----
   if (outlet) {
-    const Geo g2 = make_geo(a, x - 1, 0);
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-      const int i = OUT5[k];
-      const int hidx = (k * a.ny + y) * a.nz + z;
-      const float v = __builtin_fmaf(a.out_wh, a.hist_in[hidx], a.out_wu * pull(x - 1, g2.xs[CX[i] + 1], i));
-      f[i] = v;
-      if (mine) a.hist_out[hidx] = v;
+      const float v = __builtin_fmaf(a.out_wh, e0[k], a.out_wu * e1[k]);
+      f[OUT5[k]] = v;
+      if (mine) a.hist_out[k * a.ny * a.nz + pz] = v;
     }
   }
-  if (inlet) inlet_regularize(a, y, z, f);
+  if (inlet) inlet_regularize(e0[0], e0[1], e0[2], f);
 
   // ---- density, momentum, forces, collision (node_update) ----
   float rho = 0.f, jx = 0.f, jy = 0.f, jz = 0.f;

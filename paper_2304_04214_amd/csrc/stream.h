@@ -385,11 +385,9 @@ __device__ __forceinline__ float newton_utau(const CollideArgs& a, float ua) {
 // Regularised inlet populations (Sec. III.A, Eq. (26)-(31)): Zou-He density
 // from the known c_x <= 0 populations, second-order equilibrium at u_in, and
 // the non-equilibrium part rebuilt from Pi_neq with the unknown c_x > 0
-// non-equilibrium populations taken equal to their opposites.  Returns the
-// inlet density.
-__device__ __forceinline__ float inlet_regularize(const CollideArgs& a, int y, int z, float f[Q]) {
-  const int pl = a.ny * a.nz, o = y * a.nz + z;
-  const float ux = a.u_in[o], uy = a.u_in[pl + o], uz = a.u_in[2 * pl + o];
+// non-equilibrium populations taken equal to their opposites.  u: the inlet
+// velocity of the node.  Returns the inlet density.
+__device__ __forceinline__ float inlet_regularize(float ux, float uy, float uz, float f[Q]) {
   float rho0 = 0.f, rhom = 0.f;
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
@@ -422,6 +420,10 @@ __device__ __forceinline__ float inlet_regularize(const CollideArgs& a, int y, i
     f[i] = feq[i] + 4.5f * (float)WD[i] * (cpc - tr3);
   }
   return rin;
+}
+__device__ __forceinline__ float inlet_regularize(const CollideArgs& a, int y, int z, float f[Q]) {
+  const int pl = a.ny * a.nz, o = y * a.nz + z;
+  return inlet_regularize(a.u_in[o], a.u_in[pl + o], a.u_in[2 * pl + o], f);
 }
 
 }  // namespace lbm
