@@ -880,10 +880,6 @@ hipError_t build_block_lists(lbm_ctx* h, const std::vector<int>& plane_of_x) {
   chunk(bd, planes, nullptr, h->bnd_off);
   chunk(in, h->fused ? c.nx : chunk_planes(CHUNK_BLOCKS_F16), &in_heavy, h->int_off);
   h->chunk_planes = planes;
-  if (h->rows) {  // the row kernel is one dispatch over all planes
-    h->bnd_off = {0, (int)bd.size()};
-    h->chunk_planes = c.nx;
-  }
   hipError_t err;
   for (int k = 0; k < 2; ++k) {
     std::vector<int>& v = k == 0 ? in : bd;

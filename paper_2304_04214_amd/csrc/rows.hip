@@ -37,14 +37,14 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// rb rows of one x-plane a block, `groups` blocks a plane.  NT: non-temporal
-// population stores.
+// rb rows of one x-plane a block, `groups` blocks a plane, the planes x0 ..
+// x0 + planes - 1.  NT: non-temporal population stores.
 template <bool NT>
-__global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int rb, int groups,
+__global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int x0, int planes, int rb, int groups,
                                                             const int* __restrict__ plane_of_x) {
   __shared__ RowsLds L;
   const int gy = blockIdx.x % groups, xq = blockIdx.x / groups;
-  const int x = xq == 0 ? a.nx - 1 : xq - 1;  // the end planes, whose nodes have more to do, go first
+  const int x = x0 + (xq == 0 ? planes - 1 : xq - 1);  // the end planes, whose nodes have more to do, go first
   const bool inflow = a.xbc == LBM_X_INFLOW, walls = a.ywall != LBM_Y_PERIODIC;
   const bool bb = a.ywall == LBM_Y_BOUNCEBACK;
   const bool outlet = inflow && x == a.nx - 1, inlet = inflow && x == 0;
@@ -229,12 +229,17 @@ void plan_rows(lbm_ctx* h) {
   }
 }
 
+// One dispatch per x-range, as the general kernel.
 hipError_t launch_rows(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
-  const dim3 grid((unsigned)h->cfg.nx * h->row_groups), block(h->row_threads);
-  if (a.nt_store)
-    collide_rows_kernel<true><<<grid, block, 0, stream>>>(a, h->rows, h->row_groups, a.plane_of_x);
-  else
-    collide_rows_kernel<false><<<grid, block, 0, stream>>>(a, h->rows, h->row_groups, a.plane_of_x);
+  const dim3 block(h->row_threads);
+  for (int x0 = 0; x0 < h->cfg.nx; x0 += h->chunk_planes) {
+    const int planes = std::min(h->chunk_planes, h->cfg.nx - x0);
+    const dim3 grid((unsigned)planes * h->row_groups);
+    if (a.nt_store)
+      collide_rows_kernel<true><<<grid, block, 0, stream>>>(a, x0, planes, h->rows, h->row_groups, a.plane_of_x);
+    else
+      collide_rows_kernel<false><<<grid, block, 0, stream>>>(a, x0, planes, h->rows, h->row_groups, a.plane_of_x);
+  }
   return hipGetLastError();
 }
 
