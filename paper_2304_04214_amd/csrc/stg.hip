@@ -12,6 +12,7 @@
 
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -137,74 +138,107 @@ __global__ __launch_bounds__(256) void stg_spectrum_kernel(lbm_stg s, float* row
   if (bad) atomicOr(err, ERRBIT_STG_TABLE);
 }
 
-// One block per (inlet row y, 64 spanwise nodes, step); its four waves each
-// sum a quarter of the modes, and the partial sums are added in a fixed order.
-// Step j = blockIdx.z has time time0 + j.  With ring ==
-// nullptr the plane goes to s.u_in / s.fluct; otherwise to plane j of ring /
-// fring, and the plane of step last_j also to s.u_in / s.fluct.
+// cos and sin of ph in FP64: reduced by multiples of 2 pi (as fmod does: the
+// fused multiply-add is exact) and then of pi / 2, and the Taylor polynomials
+// of degree 16 and 17 on |x| <= pi / 4 (remainders below 1e-17).  About 40
+// FP64 instructions; fmod and sincos of the library, which reduce any argument
+// in any range, are several hundred, and the kernel below evaluates one phase
+// per row and mode in every block.
+__device__ __forceinline__ double2 cos_sin(double ph) {
+  constexpr double PIO2_HI = 1.57079632679489655800, PIO2_LO = 6.12323399573676603587e-17;
+  const double r = fma(-trunc(ph * (1.0 / TWO_PI)), TWO_PI, ph);
+  const double k = rint(r * (4.0 / TWO_PI));
+  const double x = fma(-k, PIO2_LO, fma(-k, PIO2_HI, r));
+  const double q = x * x;
+  double c = 1.0 / 20922789888000.0, s = 1.0 / 355687428096000.0;  // 1/16!, 1/17!
+  c = fma(c, q, -1.0 / 87178291200.0);
+  s = fma(s, q, -1.0 / 1307674368000.0);
+  c = fma(c, q, 1.0 / 479001600.0);
+  s = fma(s, q, 1.0 / 6227020800.0);
+  c = fma(c, q, -1.0 / 3628800.0);
+  s = fma(s, q, -1.0 / 39916800.0);
+  c = fma(c, q, 1.0 / 40320.0);
+  s = fma(s, q, 1.0 / 362880.0);
+  c = fma(c, q, -1.0 / 720.0);
+  s = fma(s, q, -1.0 / 5040.0);
+  c = fma(c, q, 1.0 / 24.0);
+  s = fma(s, q, 1.0 / 120.0);
+  c = fma(c, q, -0.5);
+  s = fma(s, q, -1.0 / 6.0);
+  c = fma(c, q, 1.0);
+  s = fma(s * q, x, x);
+  const int m = (int)k;  // quadrant
+  const double cr = m & 1 ? s : c, sr = m & 1 ? c : s;
+  return make_double2((m + 1) & 2 ? -cr : cr, m & 2 ? -sr : sr);
+}
+
+// One block per (RB inlet rows from y0, 64 spanwise nodes, step); its four
+// waves each sum a quarter of the modes for all RB rows, so that a mode's
+// spanwise factors are loaded once for them, and the partial sums are added in
+// a fixed order.  ROWAMP: the rows have amplitudes of their own (per-row
+// spectrum).  Step j = blockIdx.z has time time0 + j.  With ring == nullptr
+// the plane goes to s.u_in / s.fluct; otherwise to plane j of ring / fring, and
+// the plane of step last_j also to s.u_in / s.fluct.
+template <int RB, bool ROWAMP>
 __global__ __launch_bounds__(256) void stg_fill_kernel(lbm_stg s, StgTables t, int ny, int nz, double time0,
                                                        int* err, float* ring, float* fring, int last_j,
                                                        PlaneDst dst) {
-  __shared__ float2 rowph[LBM_MAX_MODES];
-  __shared__ float amp[3][LBM_MAX_MODES];
-  __shared__ float part[3][3][64];
+  constexpr int RA = ROWAMP ? RB : 1;
+  extern __shared__ float4 stg_lds[];  // amplitudes [RA][N], then phases [RB][N] (float2)
+  __shared__ float part[3][RB][3][64];
+  const int N = s.n_modes;
+  float4* amp = stg_lds;
+  float2* rowph = reinterpret_cast<float2*>(stg_lds + RA * N);
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int y = blockIdx.y;
+  const int y0 = blockIdx.y * RB;
   const int zr = blockIdx.x * 64 + lane;
   const int z = zr < nz ? zr : nz - 1;
-  const int N = s.n_modes;
   const int j = blockIdx.z;
   const double time = time0 + j;
-  // (y, t)-dependent phase of every mode, FP64 then reduced to [0, 2 pi)
+  // (y, t)-dependent phase of every mode, FP64 reduced to [0, 2 pi); rows beyond the last repeat it
   for (int n = threadIdx.x; n < N; n += 256) {
-    const double ph = fmod(t.ky[n] * (y + 0.5) + s.omega[n] * time + s.phi[n], TWO_PI);
-    double sn, cs;
-    sincos(ph, &sn, &cs);
-    rowph[n] = make_float2((float)cs, (float)sn);
-    const float r = t.rowamp ? t.rowamp[(int64_t)y * N + n] : 1.f;
-    amp[0][n] = t.amp3[n] * r;
-    amp[1][n] = t.amp3[N + n] * r;
-    amp[2][n] = t.amp3[2 * N + n] * r;
+    const double ky = t.ky[n], ot = s.omega[n], phi = s.phi[n];
+    const float a0 = t.amp3[n], a1 = t.amp3[N + n], a2 = t.amp3[2 * N + n];
+#pragma unroll
+    for (int k = 0; k < RB; ++k) {
+      const int y = min(y0 + k, ny - 1);
+      const double2 cs = cos_sin(ky * (y + 0.5) + ot * time + phi);
+      rowph[k * N + n] = make_float2((float)cs.x, (float)cs.y);
+      if (ROWAMP) {
+        const float r = t.rowamp[(int64_t)y * N + n];
+        amp[k * N + n] = make_float4(a0 * r, a1 * r, a2 * r, 0.f);
+      }
+    }
+    if (!ROWAMP) amp[n] = make_float4(a0, a1, a2, 0.f);
   }
   __syncthreads();
-  float v0 = 0.f, v1 = 0.f, v2 = 0.f;
+  float v[RB][3] = {};
   const float2* tz = t.trigz + z;
   // wave w sums the contiguous mode range [n0, n1)
   const int n0 = (N * w) >> 2, n1 = (N * (w + 1)) >> 2;
 #pragma unroll 8
   for (int n = n0; n < n1; ++n) {
-    const float2 a = rowph[n];
     const float2 b = tz[(int64_t)n * nz];
-    const float c = a.x * b.x - a.y * b.y;  // cos(alpha + beta)
-    v0 += amp[0][n] * c;
-    v1 += amp[1][n] * c;
-    v2 += amp[2][n] * c;
+#pragma unroll
+    for (int k = 0; k < RB; ++k) {
+      const float2 a = rowph[k * N + n];
+      const float4 m = amp[(ROWAMP ? k : 0) * N + n];
+      const float c = a.x * b.x - a.y * b.y;  // cos(alpha + beta)
+      v[k][0] += m.x * c;
+      v[k][1] += m.y * c;
+      v[k][2] += m.z * c;
+    }
   }
   if (w > 0) {
-    part[w - 1][0][lane] = v0;
-    part[w - 1][1][lane] = v1;
-    part[w - 1][2][lane] = v2;
+#pragma unroll
+    for (int k = 0; k < RB; ++k)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) part[w - 1][k][c][lane] = v[k][c];
   }
   __syncthreads();
   if (w != 0 || zr >= nz) return;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    v0 += part[k][0][lane];
-    v1 += part[k][1][lane];
-    v2 += part[k][2][lane];
-  }
-  // Eq. (23): u' = a v' with the lower-triangular Cholesky factor; Eq. (22)
-  const float a11 = t.chol[y], a21 = t.chol[ny + y], a22 = t.chol[2 * ny + y];
-  const float a31 = t.chol[3 * ny + y], a32 = t.chol[4 * ny + y], a33 = t.chol[5 * ny + y];
-  const float p0 = a11 * v0;
-  const float p1 = a21 * v0 + a22 * v1;
-  const float p2 = a31 * v0 + a32 * v1 + a33 * v2;
-  const float sb = t.sb[y];
-  const int o = y * nz + z, pl = ny * nz;
-  const float ux = t.urans[y] + sb * p0;
-  const float uy = t.urans[ny + y] + sb * p1;
-  const float uz = t.urans[2 * ny + y] + sb * p2;
+  const int pl = ny * nz;
   float* u = nullptr;
   float* f = nullptr;
   if (dst.u[0]) {  // per-step destinations (block-uniform)
@@ -215,27 +249,83 @@ __global__ __launch_bounds__(256) void stg_fill_kernel(lbm_stg s, StgTables t, i
     f = fring ? fring + (size_t)j * 3 * pl : nullptr;
   }
   const bool bound = u == nullptr || j == last_j;
-  if (u) {
-    u[o] = ux;
-    u[pl + o] = uy;
-    u[2 * pl + o] = uz;
-    if (f) {
-      f[o] = p0;
-      f[pl + o] = p1;
-      f[2 * pl + o] = p2;
+#pragma unroll
+  for (int k = 0; k < RB; ++k) {
+    const int y = y0 + k;
+    if (y >= ny) break;
+    float v0 = v[k][0], v1 = v[k][1], v2 = v[k][2];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      v0 += part[q][k][0][lane];
+      v1 += part[q][k][1][lane];
+      v2 += part[q][k][2][lane];
     }
-  }
-  if (bound) {
-    s.u_in[o] = ux;
-    s.u_in[pl + o] = uy;
-    s.u_in[2 * pl + o] = uz;
-    if (s.fluct) {
-      s.fluct[o] = p0;
-      s.fluct[pl + o] = p1;
-      s.fluct[2 * pl + o] = p2;
+    // Eq. (23): u' = a v' with the lower-triangular Cholesky factor; Eq. (22)
+    const float a11 = t.chol[y], a21 = t.chol[ny + y], a22 = t.chol[2 * ny + y];
+    const float a31 = t.chol[3 * ny + y], a32 = t.chol[4 * ny + y], a33 = t.chol[5 * ny + y];
+    const float p0 = a11 * v0;
+    const float p1 = a21 * v0 + a22 * v1;
+    const float p2 = a31 * v0 + a32 * v1 + a33 * v2;
+    const float sb = t.sb[y];
+    const int o = y * nz + z;
+    const float ux = t.urans[y] + sb * p0;
+    const float uy = t.urans[ny + y] + sb * p1;
+    const float uz = t.urans[2 * ny + y] + sb * p2;
+    if (u) {
+      u[o] = ux;
+      u[pl + o] = uy;
+      u[2 * pl + o] = uz;
+      if (f) {
+        f[o] = p0;
+        f[pl + o] = p1;
+        f[2 * pl + o] = p2;
+      }
     }
+    if (bound) {
+      s.u_in[o] = ux;
+      s.u_in[pl + o] = uy;
+      s.u_in[2 * pl + o] = uz;
+      if (s.fluct) {
+        s.fluct[o] = p0;
+        s.fluct[pl + o] = p1;
+        s.fluct[2 * pl + o] = p2;
+      }
+    }
+    if (!(fabsf(ux) < MACH_LIMIT)) atomicOr(err, ERRBIT_MACH);
   }
-  if (!(fabsf(ux) < MACH_LIMIT)) atomicOr(err, ERRBIT_MACH);
+}
+
+// The planes of nb steps, with rows per block by the number of (row, chunk,
+// step) triples: more rows share a mode's spanwise factors (with one row the
+// kernel is bound by reading them from L2), fewer spread a small plane over
+// the chip.  us a launch with 1 / 2 / 4 rows: 64x64 N = 200, one plane 4.7 /
+// 5.4 / 7.6; 128x384 N = 300, one plane (768 triples) 9.9 / 8.3 / 10.3; N =
+// 1000 27 / 21 / 26; 32 planes of it with the steps of a 3-plane lattice 487 /
+// 393 / 360.
+hipError_t fill(const lbm_stg& s, const StgTables& t, int ny, int nz, double time0, int nb, int* err, float* ring,
+                float* fring, int last_j, const PlaneDst& dst, hipStream_t stream) {
+  const int zc = (nz + 63) / 64, N = s.n_modes;
+  const int64_t work = (int64_t)zc * ny * nb;
+  auto run = [&](auto RB, auto ROWAMP) {
+    constexpr int rb = RB.value;
+    const dim3 grid(zc, (ny + rb - 1) / rb, nb);
+    const size_t lds = (size_t)N * (16 * (ROWAMP.value ? rb : 1) + 8 * rb);
+    stg_fill_kernel<rb, ROWAMP.value><<<grid, 256, lds, stream>>>(s, t, ny, nz, time0, err, ring, fring, last_j, dst);
+  };
+  const size_t lds4 = (size_t)N * (t.rowamp ? 96 : 48);  // of four rows; 64 KB hold it and the partial sums
+  auto rows = [&](auto ROWAMP) {
+    if (work >= 4096 && lds4 <= 49152)
+      run(std::integral_constant<int, 4>{}, ROWAMP);
+    else if (work >= 512)
+      run(std::integral_constant<int, 2>{}, ROWAMP);
+    else
+      run(std::integral_constant<int, 1>{}, ROWAMP);
+  };
+  if (t.rowamp)
+    rows(std::true_type{});
+  else
+    rows(std::false_type{});
+  return hipGetLastError();
 }
 
 // Reichardt law with the constants of the configuration (Sec. II.C, Eq. (16)).
@@ -294,12 +384,10 @@ hipError_t launch_stg_bind(lbm_ctx* h, const lbm_stg* s) {
 // and the inlet velocity plane).
 hipError_t launch_stg_fill(lbm_ctx* h, double time, hipStream_t stream, float* fluct, float* u_in) {
   const int ny = h->cfg.ny, nz = h->cfg.nz;
-  dim3 grid((nz + 63) / 64, ny);
   lbm_stg s = h->stg;
   if (fluct) s.fluct = fluct;
   if (u_in) s.u_in = u_in;
-  stg_fill_kernel<<<grid, 256, 0, stream>>>(s, h->tab, ny, nz, time, h->d_err, nullptr, nullptr, -1, PlaneDst{});
-  return hipGetLastError();
+  return fill(s, h->tab, ny, nz, time, 1, h->d_err, nullptr, nullptr, -1, PlaneDst{}, stream);
 }
 
 // The inlet planes of nb consecutive steps (times time0 .. time0 + nb - 1) in
@@ -308,10 +396,7 @@ hipError_t launch_stg_fill(lbm_ctx* h, double time, hipStream_t stream, float* f
 hipError_t launch_stg_fill_batch(lbm_ctx* h, double time0, int nb, hipStream_t stream, float* ring, float* fring,
                                  int last_j) {
   const int ny = h->cfg.ny, nz = h->cfg.nz;
-  dim3 grid((nz + 63) / 64, ny, nb);
-  stg_fill_kernel<<<grid, 256, 0, stream>>>(h->stg, h->tab, ny, nz, time0, h->d_err, ring, fring, last_j,
-                                            PlaneDst{});
-  return hipGetLastError();
+  return fill(h->stg, h->tab, ny, nz, time0, nb, h->d_err, ring, fring, last_j, PlaneDst{}, stream);
 }
 
 // The inlet planes of nb <= STG_BATCH consecutive steps (times time0 ..
@@ -319,9 +404,7 @@ hipError_t launch_stg_fill_batch(lbm_ctx* h, double time0, int nb, hipStream_t s
 // (both non-null for j < nb); the bound outputs are not written.
 hipError_t launch_stg_fill_to(lbm_ctx* h, double time0, int nb, hipStream_t stream, const PlaneDst& dst) {
   const int ny = h->cfg.ny, nz = h->cfg.nz;
-  dim3 grid((nz + 63) / 64, ny, nb);
-  stg_fill_kernel<<<grid, 256, 0, stream>>>(h->stg, h->tab, ny, nz, time0, h->d_err, nullptr, nullptr, -1, dst);
-  return hipGetLastError();
+  return fill(h->stg, h->tab, ny, nz, time0, nb, h->d_err, nullptr, nullptr, -1, dst, stream);
 }
 
 namespace {
@@ -413,9 +496,7 @@ hipError_t launch_stg_fill_noalloc(lbm_ctx* h, const lbm_stg* s, double time) {
     if ((e = hipGetLastError()) != hipSuccess) return e;
     t.rowamp = rowamp;
   }
-  dim3 grid((nz + 63) / 64, ny);
-  stg_fill_kernel<<<grid, 256, 0, h->stream>>>(*s, t, ny, nz, time, h->d_err, nullptr, nullptr, -1, PlaneDst{});
-  return hipGetLastError();
+  return fill(*s, t, ny, nz, time, 1, h->d_err, nullptr, nullptr, -1, PlaneDst{}, h->stream);
 }
 
 hipError_t launch_inflow_reichardt(lbm_ctx* h, double u_tau, double* u_rans) {
