@@ -19,6 +19,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "collide.h"
@@ -77,10 +78,10 @@ __device__ __forceinline__ void x_rules(const CollideArgs& a, int x, int y, int 
 }
 
 // NT: non-temporal population stores (see CollideArgs::nt_store).
-template <bool F16, bool NT = true>
+template <bool F16, bool NT = true, int ZL = ZT>
 __device__ __forceinline__ void node_update(const CollideArgs& a, int x, int y, int z, int lane, int base, int zci,
                                             bool owned, bool active, const Col& col, float f[Q],
-                                            float (*lds_u2)[2][ZT]) {
+                                            float (*lds_u2)[2][ZL]) {
   x_rules<F16>(a, x, y, z, col, f, active && owned);
 
   // density and momentum before the force (Eq. (10)-(11)), summed directly
@@ -125,7 +126,7 @@ __device__ __forceinline__ void node_update(const CollideArgs& a, int x, int y, 
         if (a.wall_acc) {  // wall statistics: sum over the wave's z of u_tau (FP64, one writer per slot)
           double v = active ? (double)ut : 0.0;
 #pragma unroll
-          for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, ZT);
+          for (int off = ZL / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, ZT);
           if (lane == 0) a.wall_acc[((size_t)w * a.nx + x) * a.zc + zci] += v;
         }
       }
@@ -144,9 +145,11 @@ __device__ __forceinline__ void node_update(const CollideArgs& a, int x, int y, 
 
   if (active && owned) {
     char* p = const_cast<char*>(row_ptr<F16>(a.dst, rowpart(a, x, y)));
+    float ref[Q];  // all loaded before the first store: between stores each would wait for its own
 #pragma unroll
-    for (int i = 0; i < Q; ++i)
-      Pop<F16>::template stp<NT>(p + i * ZT * Pop<F16>::ES, i, col.b0, f[i], ref_off(a, i, y));
+    for (int i = 0; i < Q; ++i) ref[i] = F16 ? ref_off(a, i, y) : 0.f;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) Pop<F16>::template stp<NT>(p + i * ZT * Pop<F16>::ES, i, col.b0, f[i], ref[i]);
   }
 
   if (a.stats_on) {
@@ -167,7 +170,7 @@ __device__ __forceinline__ void node_update(const CollideArgs& a, int x, int y, 
 #pragma unroll
       for (int k = 0; k < 9; ++k)
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, ZT);
+        for (int off = ZL / 2; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, ZT);
       if (lane == 0) {
         double* s = a.stats + (((size_t)p * a.ny + y) * a.zc + zci) * 9;
 #pragma unroll
@@ -190,28 +193,63 @@ __device__ __forceinline__ void node_update(const CollideArgs& a, int x, int y, 
 // block.  All read s_n and write disjoint nodes of s_{n+1}.  Each walks a
 // block list (columns (x, y-group) dealt to the XCDs by xcd_order).
 
+// Row of the calling thread in its block: rows of ZL lanes (64: one wave a row,
+// a scalar).
+template <int ZL>
+__device__ __forceinline__ int row_of_thread() {
+  return ZL == ZT ? uni(threadIdx.x >> 6) : (int)threadIdx.x / ZL;
+}
+
+// Storage offsets of the block's rows and one beyond each side, by short rows
+// (ZL < 64) from LDS: loaded before the pulls go out, stored behind them, so
+// that no pull waits for them.
+template <int ZL>
+struct RowRef {
+  static constexpr int N = (YROWS + 2) * Q, PER = (N + YROWS * ZL - 1) / (YROWS * ZL);
+  float v[PER];
+  __device__ __forceinline__ void load(const CollideArgs& a, const float* __restrict__ dref, int base) {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int k = min((int)threadIdx.x + j * YROWS * ZL, N - 1), q = k / Q;
+      int y = base - 1 + q;
+      y = y < 0 ? y + a.ny : (y >= a.ny ? y - a.ny : y);
+      v[j] = dref[y * Q + (k - q * Q)];
+    }
+  }
+  __device__ __forceinline__ void store(float* lref) const {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) lref[min((int)threadIdx.x + j * YROWS * ZL, N - 1)] = v[j];
+    __syncthreads();
+  }
+};
+
 // A block whose 3 x 3 source rows all lie inside the lattice (see the
 // block lists): plain shifted pulls, no boundary rule.
 // dref / dpull: the reference offsets (REF), passed as restrict kernel
 // arguments so that their loads need not be ordered after the stores.
-template <bool F16, bool FORCE, bool REF>
+// ZL < 64: lref takes the offsets (RowRef).
+template <bool F16, bool FORCE, bool REF, int ZL = ZT>
 __device__ __forceinline__ void plain_block(const CollideArgs& a, int x, int zci, int gy,
-                                            const float* __restrict__ dref, const float* __restrict__ dpull) {
-  const int lane = threadIdx.x & (ZT - 1);
+                                            const float* __restrict__ dref, const float* __restrict__ dpull,
+                                            float* lref = nullptr) {
+  const int lane = threadIdx.x & (ZL - 1);
   const int base = min(YROWS * gy, a.ny - YROWS);
-  const int y = base + uni(threadIdx.x >> 6);
+  const int w = row_of_thread<ZL>(), y = base + w;
   const bool owned = y >= YROWS * gy;
   const int zraw = zci * ZT + lane;
   const bool active = zraw < a.nz;
   const int z = active ? zraw : a.nz - 1;
   const Col col = make_col<F16>(a, z);
   const Geo g = make_geo(a, x, y);
+  RowRef<ZL> rr;
+  if (REF && ZL < ZT) rr.load(a, dref, base);
   typename Pop<F16>::Raw r[Q];
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
     const uint32_t cs = CZ[i] == 1 ? col.bm : (CZ[i] == -1 ? col.bp : col.b0);
     r[i] = Pop<F16>::raw(row_ptr<F16>(a.src, rowpart(a, g.xs[CX[i] + 1], g.ys[CY[i] + 1]) + (uint32_t)i * ZT), cs);
   }
+  if (REF && ZL < ZT) rr.store(lref);
   // FP16 storage computes on the deviations h = f - w directly (no w added on
   // load or subtracted on store); FP32 storage on the populations.
   float f[Q];
@@ -220,7 +258,7 @@ __device__ __forceinline__ void plain_block(const CollideArgs& a, int x, int zci
     if (!F16)
       f[i] = Pop<F16>::cvt(i, r[i], 0.f);
     else if (REF)
-      f[i] = Pop<true>::cvt_dev(r[i], dpull[y * Q + i]);  // wave-uniform row: scalar loads
+      f[i] = Pop<true>::cvt_dev(r[i], ZL < ZT ? lref[(w + 1 - CY[i]) * Q + i] : dpull[y * Q + i]);  // uniform row: scalar loads
     else
       f[i] = Pop<true>::cvt_dev(r[i]);
   }
@@ -242,7 +280,7 @@ __device__ __forceinline__ void plain_block(const CollideArgs& a, int x, int zci
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       if (F16 && REF)
-        Pop<true>::stp_dev<true>(p + i * ZT * Pop<F16>::ES, col.b0, f[i], dref[y * Q + i]);
+        Pop<true>::stp_dev<true>(p + i * ZT * Pop<F16>::ES, col.b0, f[i], ZL < ZT ? lref[(w + 1) * Q + i] : dref[y * Q + i]);
       else if (F16)
         Pop<true>::stp_dev<true>(p + i * ZT * Pop<F16>::ES, col.b0, f[i]);
       else
@@ -256,27 +294,33 @@ __device__ __forceinline__ void plain_block(const CollideArgs& a, int x, int zci
 // the wall model (the wall row's neighbour velocity through LDS).  Density
 // and momentum are summed directly so that the pair sums of the collision
 // are not live across the Newton solve (fewer registers).
-template <bool F16, bool REF>
-__device__ __forceinline__ void wall_block(const CollideArgs& a, int x, int zci, int gy, float (*lds_u2)[2][ZT],
-                                           const float* __restrict__ dref) {
-
-  const int lane = threadIdx.x & (ZT - 1);
+template <bool F16, bool REF, int ZL = ZT>
+__device__ __forceinline__ void wall_block(const CollideArgs& a, int x, int zci, int gy, float (*lds_u2)[2][ZL],
+                                           const float* __restrict__ dref, float* lref = nullptr) {
+  const int lane = threadIdx.x & (ZL - 1);
   const int base = min(YROWS * gy, a.ny - YROWS);
-  const int y = base + uni(threadIdx.x >> 6);
+  const int w = row_of_thread<ZL>(), y = base + w;
   const bool owned = y >= YROWS * gy;
   const int zraw = zci * ZT + lane;
   const bool active = zraw < a.nz;
   const int z = active ? zraw : a.nz - 1;
   const Col col = make_col<F16>(a, z);
   const Geo g = make_geo(a, x, y);
+  RowRef<ZL> rr;
+  if (REF && ZL < ZT) rr.load(a, dref, base);
   typename Pop<F16>::Raw r[Q];
-  issue_pulls<F16>(a, g, col, r);  // every x source exists; the y walls redirect
+  issue_pulls<F16, ZL == ZT>(a, g, col, r);  // every x source exists; the y walls redirect
+  if (REF && ZL < ZT) rr.store(lref);
   float f[Q];
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
-    if (!F16)
+    if (!F16) {
       f[i] = Pop<F16>::cvt(i, r[i], 0.f);
-    else if (REF)
+    } else if (REF && ZL < ZT) {
+      int plane, ysrc;
+      pull_plane_row(a, g, i, plane, ysrc);
+      f[i] = Pop<true>::cvt_dev(r[i], lref[(CY[i] != 0 && g.yout[CY[i] + 1] ? w + 1 : w + 1 - CY[i]) * Q + plane]);
+    } else if (REF)
       f[i] = Pop<true>::cvt_dev(r[i], pull_ref(a, g, i));
     else
       f[i] = Pop<true>::cvt_dev(r[i]);
@@ -307,16 +351,16 @@ __device__ __forceinline__ void wall_block(const CollideArgs& a, int x, int zci,
     __syncthreads();
     const bool wb = bot && y == 0, wt = top && y == a.ny - 1;
     if (wb || wt) {
-      const int w = wb ? 0 : 1;
+      const int wl = wb ? 0 : 1;
       float fwx, fwz, ut;
-      wall_force(a, rho, jx * ir, jz * ir, lds_u2[w][0][lane], lds_u2[w][1][lane], fwx, fwz, ut, w, x);
+      wall_force(a, rho, jx * ir, jz * ir, lds_u2[wl][0][lane], lds_u2[wl][1][lane], fwx, fwz, ut, wl, x);
       Fx += fwx;
       Fz += fwz;
       if (a.wall_acc) {
         double v = active ? (double)ut : 0.0;
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, ZT);
-        if (lane == 0) a.wall_acc[((size_t)w * a.nx + x) * a.zc + zci] += v;
+        for (int off = ZL / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, ZT);
+        if (lane == 0) a.wall_acc[((size_t)wl * a.nx + x) * a.zc + zci] += v;
       }
     }
   }
@@ -329,7 +373,7 @@ __device__ __forceinline__ void wall_block(const CollideArgs& a, int x, int zci,
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       if (F16 && REF)
-        Pop<true>::stp_dev<true>(p + i * ZT * Pop<F16>::ES, col.b0, f[i], dref[y * Q + i]);
+        Pop<true>::stp_dev<true>(p + i * ZT * Pop<F16>::ES, col.b0, f[i], ZL < ZT ? lref[(w + 1) * Q + i] : dref[y * Q + i]);
       else if (F16)
         Pop<true>::stp_dev<true>(p + i * ZT * Pop<F16>::ES, col.b0, f[i]);
       else
@@ -379,26 +423,38 @@ __global__ __launch_bounds__(BLOCK) void collide_general_kernel(CollideArgs a, c
   node_update<F16, NT>(a, x, y, z, lane, base, zci, owned, active, col, f, lds_u2);
 }
 
+// Waves per SIMD that the fused kernel with short rows is held to: 71 VGPRs
+// without spills.  At eight, as with 64-lane rows, it spills and loses what the
+// short rows give (400x40x32: 20.6 us per step at six, 26.3 at eight).
+constexpr int FUSED_SHORT_WAVES = 6;
+
 // FP16 storage on lattices up to FUSED_MAX_NODES: both block lists in one
 // launch, the general blocks (gl, n_gen entries) first so that their longer
 // work overlaps the bulk blocks (bl).  Held to 64 VGPRs (8 waves per SIMD, as
 // the bulk kernel; the general path spills a few).  A separate general launch
 // costs a fixed ~10 us (its blocks run alone as a latency-bound wave), more
 // than the fused kernel's slower bulk path on small lattices, less on large.
-template <bool F16, bool FORCE, bool REF>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8)))
+//
+// ZL: lanes of a row.  Lattices of at most 32 (16) spanwise nodes give a row 32
+// (16) lanes, so that a wave holds two (four) rows of the block's four and
+// fewer lanes are without a node.  us per step with 64 lanes -> with these:
+// 400x40x32 24.1 -> 20.6, 64x32x32 9.9 -> 7.6, 600x60x24 32.2 -> 28.7,
+// 200x20x16 13.4 -> 10.3, 880x80x16 56.0 -> 55.1 (bound by the padded bricks'
+// 128-byte lines).
+template <bool F16, bool FORCE, bool REF, int ZL>
+__global__ __launch_bounds__(YROWS* ZL) __attribute__((amdgpu_waves_per_eu(ZL == ZT ? 8 : FUSED_SHORT_WAVES)))
 void collide_fused_kernel(CollideArgs a, const int* __restrict__ gl, int n_gen, const int* __restrict__ bl,
                           const float* __restrict__ dref, const float* __restrict__ dpull) {
-  __shared__ float lds_u2[2][2][ZT];
+  __shared__ float lds_u2[2][2][ZL];
   const int b = (int)blockIdx.x;
   if (b < n_gen) {  // a general block (block-uniform)
     const int e = gl[b];
     if (e < 0) return;  // padding of the XCD-ordered list (whole block)
     int x, zci, gy;
     block_coords(a, e, x, zci, gy);
-    const int lane = threadIdx.x & (ZT - 1);
+    const int lane = threadIdx.x & (ZL - 1);
     const int base = min(YROWS * gy, a.ny - YROWS);
-    const int y = base + uni(threadIdx.x >> 6);
+    const int y = base + row_of_thread<ZL>();
     const bool owned = y >= YROWS * gy;
     const int zraw = zci * ZT + lane;
     const bool active = zraw < a.nz;
@@ -406,10 +462,10 @@ void collide_fused_kernel(CollideArgs a, const int* __restrict__ gl, int n_gen, 
     const Col col = make_col<F16>(a, z);
     const Geo g = make_geo(a, x, y);
     typename Pop<F16>::Raw r[Q];
-    issue_pulls<F16>(a, g, col, r);
+    issue_pulls<F16, ZL == ZT>(a, g, col, r);
     float f[Q];
-    convert_pulls<F16>(a, g, r, f);
-    node_update<F16>(a, x, y, z, lane, base, zci, owned, active, col, f, lds_u2);
+    convert_pulls<F16, ZL == ZT>(a, g, r, f);
+    node_update<F16, true, ZL>(a, x, y, z, lane, base, zci, owned, active, col, f, lds_u2);
     return;
   }
   const int e = bl[b - n_gen];
@@ -417,10 +473,11 @@ void collide_fused_kernel(CollideArgs a, const int* __restrict__ gl, int n_gen, 
   int x, zci, gy;
   block_coords(a, e, x, zci, gy);
   const int base = min(YROWS * gy, a.ny - YROWS);
+  __shared__ float lref[REF && ZL < ZT ? RowRef<ZL>::N : 1];
   if (a.ywall != LBM_Y_PERIODIC && (base == 0 || base == a.ny - YROWS))
-    wall_block<F16, REF>(a, x, zci, gy, lds_u2, dref);
+    wall_block<F16, REF, ZL>(a, x, zci, gy, lds_u2, dref, lref);
   else
-    plain_block<F16, FORCE, REF>(a, x, zci, gy, dref, dpull);
+    plain_block<F16, FORCE, REF, ZL>(a, x, zci, gy, dref, dpull, lref);
 }
 
 // Pre-force velocity (u_x, u_z) of node (x, y, z) after streaming and the
@@ -689,17 +746,17 @@ void launch_bulk_kernel(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
     const int ng = h->n_bnd, nt = ng + n;
     const int* gl = h->d_blist_bnd;
     if (nt == 0) return;
-    if (a.dref) {
-      if (a.has_g)
-        collide_fused_kernel<true, true, true><<<nt, BLOCK, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
+    auto go = [&](auto FORCE, auto REF) {
+      constexpr bool F = FORCE.value, R = REF.value;
+      if (h->cfg.nz <= 16)
+        collide_fused_kernel<true, F, R, 16><<<nt, YROWS * 16, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
+      else if (h->cfg.nz <= 32)
+        collide_fused_kernel<true, F, R, 32><<<nt, YROWS * 32, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
       else
-        collide_fused_kernel<true, false, true><<<nt, BLOCK, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
-    } else {
-      if (a.has_g)
-        collide_fused_kernel<true, true, false><<<nt, BLOCK, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
-      else
-        collide_fused_kernel<true, false, false><<<nt, BLOCK, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
-    }
+        collide_fused_kernel<true, F, R, ZT><<<nt, BLOCK, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
+    };
+    auto ref = [&](auto FORCE) { a.dref ? go(FORCE, std::true_type{}) : go(FORCE, std::false_type{}); };
+    a.has_g ? ref(std::true_type{}) : ref(std::false_type{});
     return;
   }
   // one dispatch per x-chunk of the list (see CHUNK_BLOCKS_F16)

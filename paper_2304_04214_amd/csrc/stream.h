@@ -213,10 +213,12 @@ __device__ __forceinline__ bool interior(const Geo& g) {
 
 // Issue the 19 pull loads of node row g (raw storage values, no conversion),
 // so that they can be in flight while another row is being collided.
-template <bool F16>
+// UNIFORM: the row is the same in every lane of a wave (otherwise the shorter
+// code of interior rows would come on top of the general one).
+template <bool F16, bool UNIFORM = true>
 __device__ __forceinline__ void issue_pulls(const CollideArgs& a, const Geo& g, const Col& col,
                                             typename Pop<F16>::Raw r[Q]) {
-  if (interior(g)) {
+  if (UNIFORM && interior(g)) {
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       const uint32_t cs = CZ[i] == 1 ? col.bm : (CZ[i] == -1 ? col.bp : col.b0);
@@ -262,10 +264,10 @@ __device__ __forceinline__ float pull_ref(const CollideArgs& a, const Geo& g, in
 }
 
 // Populations from the raw loads; sources outside the x range give 0.
-template <bool F16>
+template <bool F16, bool UNIFORM = true>
 __device__ __forceinline__ void convert_pulls(const CollideArgs& a, const Geo& g, const typename Pop<F16>::Raw r[Q],
                                               float f[Q]) {
-  if (interior(g)) {
+  if (UNIFORM && interior(g)) {
 #pragma unroll
     for (int i = 0; i < Q; ++i) f[i] = Pop<F16>::cvt(i, r[i], ref_off(a, i, g.ys[CY[i] + 1]));
   } else {
