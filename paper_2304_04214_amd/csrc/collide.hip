@@ -908,9 +908,22 @@ hipError_t build_block_lists(lbm_ctx* h, const std::vector<int>& plane_of_x) {
       }
     }
   }
+  const int per_plane = h->zc * h->yg;
+  // General blocks: the outlet plane's, the sampled planes' and the inlet plane's
+  // first, so that the longest are not the launch's tail (256x64x64 FP32 27.2 ->
+  // 26.2 us per step, 64x64x64 11.1 -> 9.9, 768x64x192 242 -> 239).
+  auto first_the_longest = [&](std::vector<int>& v) {
+    const bool open = c.xbc == LBM_X_INFLOW;
+    std::vector<int> part[4];
+    for (int e : v) {
+      const int x = e / per_plane;
+      part[open && x == c.nx - 1 ? 0 : (plane_of_x[x] >= 0 ? 1 : (open && x == 0 ? 2 : 3))].push_back(e);
+    }
+    v.clear();
+    for (const std::vector<int>& p : part) v.insert(v.end(), p.begin(), p.end());
+  };
   // Cut a list in memory order (x-major: an x-range is a contiguous run of it)
   // into ranges of `planes` planes, each ordered for the XCDs.
-  const int per_plane = h->zc * h->yg;
   auto chunk = [&](std::vector<int>& v, int planes, const std::vector<char>* heavy, std::vector<int>& off) {
     std::vector<int> out;
     off.assign(1, 0);
@@ -923,6 +936,7 @@ hipError_t build_block_lists(lbm_ctx* h, const std::vector<int>& plane_of_x) {
         part.push_back(v[i++]);
       }
       if (part.empty()) continue;
+      if (!heavy) first_the_longest(part);
       part = xcd_order(part, h->zc, heavy ? &hv : nullptr);
       out.insert(out.end(), part.begin(), part.end());
       off.push_back((int)out.size());
