@@ -395,13 +395,22 @@ lbm_status lbm_stats(lbm_handle h, int32_t op, const int32_t* x_planes, int32_t 
         if (x < 0 || x >= nx || map[x] >= 0) return LBM_ERR_ARG;
         map[x] = p;
       }
+      const size_t bytes = sizeof(double) * (size_t)n_planes * ny * h->zc * 9;
+      if (h->d_stats && h->stats_bytes == bytes && map == h->plane_of_x) {
+        // the planes attached before: buffers and block lists are theirs
+        HIPCHK(hipMemsetAsync(h->d_stats, 0, bytes, h->stream));
+        if (h->d_wall_acc) HIPCHK(hipMemsetAsync(h->d_wall_acc, 0, sizeof(double) * 2 * nx * h->zc, h->stream));
+        h->n_samples = 0;
+        h->stats_on = 1;
+        return LBM_OK;
+      }
       HIPCHK(hipStreamSynchronize(h->stream));
       if (h->d_stats) {
         HIPCHK(hipFree(h->d_stats));
         h->d_stats = nullptr;
       }
-      const size_t bytes = sizeof(double) * (size_t)n_planes * ny * h->zc * 9;
       HIPCHK(hipMalloc(&h->d_stats, bytes));
+      h->stats_bytes = bytes;
       HIPCHK(hipMemsetAsync(h->d_stats, 0, bytes, h->stream));
       if (h->cfg.wall_model && !h->d_wall_acc) HIPCHK(hipMalloc(&h->d_wall_acc, sizeof(double) * 2 * nx * h->zc));
       if (h->d_wall_acc) HIPCHK(hipMemsetAsync(h->d_wall_acc, 0, sizeof(double) * 2 * nx * h->zc, h->stream));

@@ -140,6 +140,7 @@ struct lbm_ctx {
   // 0: not used), its threads and its blocks per plane.
   int rows = 0, row_threads = 0, row_groups = 0;
   double* d_stats = nullptr;
+  size_t stats_bytes = 0;
   double* d_wall_acc = nullptr;  // [2][nx][zc], with the wall model
   float* d_wall_line = nullptr;  // [2][nx] line-averaged u_tau of the current step
   double* d_line_part = nullptr; // [2][nx][zc] adjoint partial sums of the line model
