@@ -409,8 +409,8 @@ lbm_status lbm_stats(lbm_handle h, int32_t op, const int32_t* x_planes, int32_t 
         HIPCHK(hipFree(h->d_stats));
         h->d_stats = nullptr;
       }
+      h->stats_bytes = 0;  // until the buffers and the lists are all these planes'
       HIPCHK(hipMalloc(&h->d_stats, bytes));
-      h->stats_bytes = bytes;
       HIPCHK(hipMemsetAsync(h->d_stats, 0, bytes, h->stream));
       if (h->cfg.wall_model && !h->d_wall_acc) HIPCHK(hipMalloc(&h->d_wall_acc, sizeof(double) * 2 * nx * h->zc));
       if (h->d_wall_acc) HIPCHK(hipMemsetAsync(h->d_wall_acc, 0, sizeof(double) * 2 * nx * h->zc, h->stream));
@@ -421,6 +421,7 @@ lbm_status lbm_stats(lbm_handle h, int32_t op, const int32_t* x_planes, int32_t 
       h->stats_on = 1;
       h->plane_of_x = map;
       HIPCHK(lbm::build_block_lists(h, h->plane_of_x));
+      h->stats_bytes = bytes;
       return LBM_OK;
     }
     case LBM_STATS_DETACH:
