@@ -373,6 +373,22 @@ lbm_status lbm_step_record(lbm_handle h, const lbm_stg* stg, const void* s_start
                            double t_start, int32_t nsteps, void* const* f_out, float* const* hist_out,
                            float* const* uin_out, float* const* fluct_out);
 
+/*
+ * nsteps steps as lbm_step, keeping what an adjoint sweep over them reads, so
+ * that it needs no recompute.  The handle's current buffer keeps the state at
+ * the start, f_keep[k] and hist_keep[k] receive the state after step k for
+ * k < nsteps - 1, and the last step writes the handle's other buffer, the
+ * current one on return.  uin_keep[k] and fluct_keep[k] receive the inlet
+ * plane that step k used; the last one's also goes to the bound u_in / fluct.
+ * Host arrays of nsteps - 1 (f_keep, hist_keep) and nsteps device pointers,
+ * buffers as for lbm_create / lbm_stg, none of them the handle's own and
+ * consecutive ones different; hist_keep, uin_keep and fluct_keep are required
+ * with LBM_X_INFLOW and not read without.  Statistics accumulate as in
+ * lbm_step.  Errors: as lbm_step, LBM_ERR_SHAPE (alignment of f_keep).
+ */
+lbm_status lbm_step_keep(lbm_handle h, const lbm_stg* stg, int32_t nsteps, void* const* f_keep,
+                         float* const* hist_keep, float* const* uin_keep, float* const* fluct_keep);
+
 /* Float brick field (an adjoint field lam) <-> float SoA [19][N], device buffers. */
 lbm_status lbm_field_export(lbm_handle h, const float* bricks, float* soa);
 lbm_status lbm_field_import(lbm_handle h, const float* soa, float* bricks);

@@ -310,6 +310,15 @@ class Channel:
                                      arr(f_out), arr(hist_out), arr(uin_out), arr(fluct_out))
         A.check(st, "lbm_step_record")
 
+    def step_keep(self, n, f_keep, hist_keep, uin_keep, fluct_keep):
+        """n steps as step(), keeping the states between (n - 1 buffers) and the inlet planes (n): the
+        state at the start stays in its buffer, the last one is the current state."""
+        assert len(f_keep) == len(hist_keep) == max(n - 1, 0) and len(uin_keep) == len(fluct_keep) == n
+        arr = lambda ts: (C.c_void_p * max(len(ts), 1))(*[t.data_ptr() for t in ts])
+        st = A.lib().lbm_step_keep(self._h, self._stg_arg(), int(n), arr(f_keep), arr(hist_keep), arr(uin_keep),
+                                   arr(fluct_keep))
+        A.check(st, "lbm_step_keep")
+
     # ---- timing ----
     def kernel_timing(self, enable):
         """(summed ms, launches, nodes per launch) of the timed interior collide kernel."""

@@ -334,6 +334,45 @@ hipError_t enqueue_steps(lbm_ctx* h, int cur, int64_t time, int32_t nsteps, hipS
   return hipSuccess;
 }
 
+// As enqueue_steps from the handle's state on its stream, the states between
+// in the caller's buffers: the handle's buffer pointers are moved along, and
+// put back by the caller.
+static hipError_t enqueue_kept(lbm_ctx* h, int32_t nsteps, void* const* f_keep, float* const* hist_keep,
+                        float* const* uin_keep, float* const* fluct_keep) {
+  const bool inflow = h->cfg.xbc == LBM_X_INFLOW;
+  void* const f_last = h->f[1 - h->cur];
+  float* const hist_last = h->hist[1 - h->cur];
+  void* src = h->f[h->cur];
+  float* hsrc = h->hist[h->cur];
+  hipError_t e;
+  for (int32_t n = 0; n < nsteps; ++n) {
+    if (inflow && n % lbm::STG_BATCH == 0) {
+      const int nb = (int)std::min<int64_t>(lbm::STG_BATCH, nsteps - n);
+      lbm::PlaneDst dst{};
+      for (int j = 0; j < nb; ++j) {
+        dst.u[j] = uin_keep[n + j];
+        dst.f[j] = fluct_keep[n + j];
+      }
+      if ((e = lbm::launch_stg_fill_to(h, (double)(h->time + n + 1), nb, h->stream, dst)) != hipSuccess) return e;
+    }
+    const bool last = n == nsteps - 1;
+    h->f[0] = src;
+    h->f[1] = last ? f_last : f_keep[n];
+    h->hist[0] = hsrc;
+    h->hist[1] = last ? hist_last : (inflow ? hist_keep[n] : nullptr);
+    const float* u = inflow ? uin_keep[n] : nullptr;
+    if (h->split && (e = lbm::launch_boundary(h, 0, 1, h->stream, u)) != hipSuccess) return e;
+    if ((e = timed_launch(h, 0, 1, u, h->stream)) != hipSuccess) return e;
+    src = h->f[1];
+    hsrc = h->hist[1];
+  }
+  if (!inflow) return hipSuccess;
+  const size_t bytes = sizeof(float) * 3 * (size_t)h->cfg.ny * h->cfg.nz;
+  e = hipMemcpyAsync(h->stg.u_in, uin_keep[nsteps - 1], bytes, hipMemcpyDeviceToDevice, h->stream);
+  if (e != hipSuccess || !h->stg.fluct) return e;
+  return hipMemcpyAsync(h->stg.fluct, fluct_keep[nsteps - 1], bytes, hipMemcpyDeviceToDevice, h->stream);
+}
+
 lbm_status lbm_step(lbm_handle h, const lbm_stg* stg, int32_t nsteps) {
   if (!h || nsteps < 0) return LBM_ERR_ARG;
   if (stg) {
@@ -528,6 +567,41 @@ lbm_status lbm_step_record(lbm_handle h, const lbm_stg* stg, const void* s_start
     HIPCHK(lbm::launch_step_explicit(h, src, f_out[k], hsrc, inflow ? hist_out[k] : nullptr, inflow ? uin : nullptr,
                                      h->stream));
   }
+  return LBM_OK;
+}
+
+lbm_status lbm_step_keep(lbm_handle h, const lbm_stg* stg, int32_t nsteps, void* const* f_keep,
+                         float* const* hist_keep, float* const* uin_keep, float* const* fluct_keep) {
+  if (!h || nsteps < 0 || (nsteps > 1 && !f_keep)) return LBM_ERR_ARG;
+  const bool inflow = h->cfg.xbc == LBM_X_INFLOW;
+  if (inflow && ((nsteps > 1 && !hist_keep) || (nsteps > 0 && (!uin_keep || !fluct_keep)))) return LBM_ERR_ARG;
+  for (int32_t k = 0; k < nsteps; ++k) {
+    if (inflow && (!uin_keep[k] || !fluct_keep[k])) return LBM_ERR_ARG;
+    if (k == nsteps - 1) break;
+    if (!f_keep[k] || f_keep[k] == h->f[0] || f_keep[k] == h->f[1] || (k > 0 && f_keep[k] == f_keep[k - 1]))
+      return LBM_ERR_ARG;
+    if (!aligned256(f_keep[k])) return LBM_ERR_SHAPE;
+    if (inflow && (!hist_keep[k] || hist_keep[k] == h->hist[0] || hist_keep[k] == h->hist[1] ||
+                   (k > 0 && hist_keep[k] == hist_keep[k - 1])))
+      return LBM_ERR_ARG;
+  }
+  if (stg) {
+    lbm_status st = bind_stg(h, stg);
+    if (st != LBM_OK) return st;
+  }
+  if (inflow && !h->stg_bound) return LBM_ERR_STATE;
+  if (nsteps == 0) return LBM_OK;
+  void* const f[2] = {h->f[0], h->f[1]};
+  float* const hist[2] = {h->hist[0], h->hist[1]};
+  const hipError_t e = enqueue_kept(h, nsteps, f_keep, hist_keep, uin_keep, fluct_keep);
+  for (int k = 0; k < 2; ++k) {
+    h->f[k] = f[k];
+    h->hist[k] = hist[k];
+  }
+  HIPCHK(e);
+  h->cur = 1 - h->cur;
+  h->time += nsteps;
+  if (h->stats_on) h->n_samples += nsteps;
   return LBM_OK;
 }
 
