@@ -909,15 +909,19 @@ hipError_t build_block_lists(lbm_ctx* h, const std::vector<int>& plane_of_x) {
     }
   }
   const int per_plane = h->zc * h->yg;
-  // General blocks: the outlet plane's, the sampled planes' and the inlet plane's
-  // first, so that the longest are not the launch's tail (256x64x64 FP32 27.2 ->
-  // 26.2 us per step, 64x64x64 11.1 -> 9.9, 768x64x192 242 -> 239).
+  // General blocks: the outlet plane's and the inlet plane's first, so that the
+  // longest are not the launch's tail (256x64x64 FP32 27.2 -> 26.2 us per step,
+  // 768x64x192 242 -> 239).  The sampled planes' too where the launch is little
+  // more than one round of blocks (64x64x64 10.9 -> 9.9 us); on larger lattices
+  // they are no tail, and many of them out of turn cost (128x96x336 with twelve,
+  // 112 -> 114.5).
   auto first_the_longest = [&](std::vector<int>& v) {
     const bool open = c.xbc == LBM_X_INFLOW;
+    const bool one_round = v.size() <= 2048;
     std::vector<int> part[4];
     for (int e : v) {
       const int x = e / per_plane;
-      part[open && x == c.nx - 1 ? 0 : (plane_of_x[x] >= 0 ? 1 : (open && x == 0 ? 2 : 3))].push_back(e);
+      part[open && x == c.nx - 1 ? 0 : (one_round && plane_of_x[x] >= 0 ? 1 : (open && x == 0 ? 2 : 3))].push_back(e);
     }
     v.clear();
     for (const std::vector<int>& p : part) v.insert(v.end(), p.begin(), p.end());
