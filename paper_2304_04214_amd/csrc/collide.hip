@@ -684,12 +684,11 @@ void fill_args(lbm_ctx* h, CollideArgs& a, int src, int dst) {
   a.wall_law = c.wall_law;
   a.newton_iters = c.newton_iters;
   a.stats_on = h->stats_on && h->d_stats != nullptr;
-  // FP32 population stores bypass the caches (non-temporal) unless both state
-  // buffers fit in the Infinity Cache with room to spare: then the next step
-  // reads the state the last one wrote from there.  (FP16 storage measured
+  // FP32 population stores bypass the caches (non-temporal) unless the next
+  // step finds much of the state the last one wrote in the Infinity Cache.  (FP16 storage measured
   // no gain from cached stores: it always stores non-temporally.)
   a.nt_store = h->cfg.storage == LBM_STORE_F16DEV ||
-               2 * 4 * (int64_t)Q * h->cfg.nx * h->cfg.ny * h->zc * ZT > NT_STORE_MIN_BYTES;
+               touched_bytes(h->cfg) > NT_STORE_MIN_BYTES;
   a.has_g = (c.g[0] != 0.0 || c.g[1] != 0.0 || c.g[2] != 0.0) ? 1 : 0;
   a.tau0 = (float)c.tau0;
   a.tau0sq = (float)(c.tau0 * c.tau0);

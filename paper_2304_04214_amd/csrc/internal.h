@@ -25,18 +25,24 @@ constexpr int64_t FUSED_MAX_NODES = int64_t(1) << 24;  // FP16: one fused collid
 // range of x-planes holding about this many blocks (whole planes; a lattice of
 // up to 1.5x this many blocks is one dispatch).  On lattices of tens of
 // millions of nodes this holds the pull at about 0.75 of HBM peak where one
-// dispatch over all blocks reaches 0.69-0.70; the FP16 bulk kernel gains
-// nothing from it and keeps one dispatch.
+// dispatch over all blocks reaches 0.69-0.70; the FP16 bulk kernel has
+// its own number below.
 constexpr int CHUNK_BLOCKS = 30000;
 // FP16 storage: the bulk kernel's blocks likewise, in dispatches of about this
 // many.  1536x128x384, us per step where one dispatch takes 980: 384 planes
 // (74,000 blocks) 934, 192 planes 950, 128 planes 968, 64 planes 1032; on a second
 // MI355X, by this constant: 50,000 949, 74,000 953, 100,000 961, 150,000 977.
 constexpr int CHUNK_BLOCKS_F16 = 60000;
-// FP32 state buffers together larger than this: non-temporal population
-// stores (the 256 MB Infinity Cache cannot hold the state from one step to
-// the next).
-constexpr int64_t NT_STORE_MIN_BYTES = int64_t(192) << 20;
+// FP32 storage, where the 128-byte lines that the nodes of both state buffers
+// touch are together more than this: non-temporal population stores (the 256 MB
+// Infinity Cache holds too little of the state from one step to the next).  us
+// per step, non-temporal -> cached: 400x64x64 (249 MB) 44.5 -> 38.9, 480x64x64
+// (299 MB) 52.6 -> 47.8, 520x64x64 (324 MB) 56.8 -> 59.2.
+constexpr int64_t NT_STORE_MIN_BYTES = int64_t(288) << 20;
+inline int64_t touched_bytes(const lbm_config& c) {
+  const int64_t line = 128, rest = 4 * (c.nz % ZT);
+  return 2 * (int64_t)Q * c.nx * c.ny * (c.nz / ZT * 4 * ZT + (rest + line - 1) / line * line);
+}
 // Static device scratch of stg_inlet_fill_noalloc (per device, for the process
 // lifetime): the STG tables of one call must fit.
 constexpr size_t NOALLOC_STG_BYTES = size_t(4) << 20;

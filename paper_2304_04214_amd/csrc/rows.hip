@@ -10,7 +10,7 @@
 // blocks on small lattices, on large ones by the 128-byte lines of the padded
 // bricks, of which nz = 16 uses half.  Per step, general kernel -> this one:
 // 200x20x16 8.2 -> 6.5 us, 64x32x32 7.3 -> 6.3, 400x40x32 18.5 -> 15.3,
-// 880x80x16 60 -> 56.
+// 603x63x16 39.7 -> 24.6, 603x63x28 41.7 -> 34.0.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -38,8 +38,9 @@ __device__ __forceinline__ double wave_sum(double v) {
 }
 
 // rb rows of one x-plane a block, `groups` blocks a plane, the planes x0 ..
-// x0 + planes - 1.  NT: non-temporal population stores.
-template <bool NT>
+// x0 + planes - 1.  The stores go through the caches: blocks end within rows,
+// and lines written in parts bypassing the caches cost more than what the next
+// step reads (521x60x16 27.9 -> 21.2 us per step, 347x60x24 24.3 -> 18.0).
 __global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int x0, int planes, int rb, int groups,
                                                             const int* __restrict__ plane_of_x) {
   __shared__ RowsLds L;
@@ -163,7 +164,7 @@ __global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int x
   if (mine) {
     char* d = static_cast<char*>(a.dst) + (size_t)x * plane;
 #pragma unroll
-    for (int i = 0; i < Q; ++i) Pop<false>::stp<NT>(d + i * (ZT * 4), i, self, f[i], 0.f);
+    for (int i = 0; i < Q; ++i) Pop<false>::stp<false>(d + i * (ZT * 4), i, self, f[i], 0.f);
   }
 
   // ---- statistics: sums over z (nz <= 32, so one wave holds a row) of the block's own rows ----
@@ -202,9 +203,12 @@ __global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int x
 }  // namespace
 
 // Rows per block and blocks per plane of the row kernel (0 rows: not used).
-// FP32 storage with nz <= 32: beyond that a row's segments no longer begin on
-// 64-byte borders of the waves' accesses and the kernel loses (500x150x36 155
-// -> 166-197 us per step, 300x90x85 76 -> 78-87).  The rows are those that
+// FP32 storage with nz <= 32, where a step's stores stay in the caches for the
+// next (NT_STORE_MIN_BYTES): us per step, general kernel -> this one, 625x96x24
+// (60,000 rows) 58.5 -> 48.3, 687x104x28 (71,000) 65 -> 108, with non-temporal
+// stores 82.  Beyond 32 a row leaves less than half the wave idle and little is
+// won by more nodes a wave (190x63x48 18.3 -> 18.4, 400x75x40 42.5 -> 46.5).
+// The rows are those that
 // leave the fewest threads without a row of their own.  Up to 2^17 nodes the
 // chip takes all blocks in one round and the smallest such blocks are taken
 // (200x20x16: 6.5 us per step with one wave a block, 7.4 with two of which a
@@ -214,7 +218,7 @@ __global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int x
 void plan_rows(lbm_ctx* h) {
   const lbm_config& c = h->cfg;
   h->rows = 0;
-  if (c.storage != LBM_STORE_F32 || c.nz > MAXZ) return;
+  if (c.storage != LBM_STORE_F32 || c.nz > MAXZ || touched_bytes(c) > NT_STORE_MIN_BYTES) return;
   const bool small = h->N <= (int64_t(1) << 17);
   const int most = std::min((small ? MAXT / 2 : MAXT) / c.nz, c.ny);
   int64_t least = 0;  // threads of a plane
@@ -235,10 +239,7 @@ hipError_t launch_rows(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
   for (int x0 = 0; x0 < h->cfg.nx; x0 += h->chunk_planes) {
     const int planes = std::min(h->chunk_planes, h->cfg.nx - x0);
     const dim3 grid((unsigned)planes * h->row_groups);
-    if (a.nt_store)
-      collide_rows_kernel<true><<<grid, block, 0, stream>>>(a, x0, planes, h->rows, h->row_groups, a.plane_of_x);
-    else
-      collide_rows_kernel<false><<<grid, block, 0, stream>>>(a, x0, planes, h->rows, h->row_groups, a.plane_of_x);
+    collide_rows_kernel<<<grid, block, 0, stream>>>(a, x0, planes, h->rows, h->row_groups, a.plane_of_x);
   }
   return hipGetLastError();
 }

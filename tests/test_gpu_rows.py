@@ -32,6 +32,9 @@ CASES = {
     "line-averaged": ((5, 11, 24), dict(ywall="slip", xbc="inflow", wall_model=True, wall_avg="line")),
     # above 2^17 nodes: blocks of 256 threads
     "large": ((260, 20, 27), dict(ywall="slip", xbc="inflow", wall_model=True)),
+    # the two sides of the number of rows up to which the row kernel is taken
+    "most-rows": ((620, 100, 4), dict(ywall="slip", xbc="inflow", wall_model=True)),
+    "too-many-rows": ((622, 100, 4), dict(ywall="slip", xbc="inflow", wall_model=True)),
 }
 
 
@@ -39,7 +42,7 @@ CASES = {
 def test_fields_and_statistics_match_the_oracle(name):
     shape, kw = CASES[name]
     print("rows", name, shape, flush=True)
-    steps = 4 if name == "large" else 20
+    steps = 4 if shape[0] > 100 else 20
     c = Case(*shape, **kw)
     planes = [0, 1, shape[0] - 1]
     c.ch.stats_attach(planes)
