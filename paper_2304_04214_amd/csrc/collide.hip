@@ -228,7 +228,7 @@ struct RowRef {
 // dref / dpull: the reference offsets (REF), passed as restrict kernel
 // arguments so that their loads need not be ordered after the stores.
 // ZL < 64: lref takes the offsets (RowRef).
-template <bool F16, bool FORCE, bool REF, int ZL = ZT>
+template <bool F16, bool FORCE, bool REF, bool NT = true, int ZL = ZT>
 __device__ __forceinline__ void plain_block(const CollideArgs& a, int x, int zci, int gy,
                                             const float* __restrict__ dref, const float* __restrict__ dpull,
                                             float* lref = nullptr) {
@@ -280,11 +280,11 @@ __device__ __forceinline__ void plain_block(const CollideArgs& a, int x, int zci
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       if (F16 && REF)
-        Pop<true>::stp_dev<true>(p + i * ZT * Pop<F16>::ES, col.b0, f[i], ZL < ZT ? lref[(w + 1) * Q + i] : dref[y * Q + i]);
+        Pop<true>::stp_dev<NT>(p + i * ZT * Pop<F16>::ES, col.b0, f[i], ZL < ZT ? lref[(w + 1) * Q + i] : dref[y * Q + i]);
       else if (F16)
-        Pop<true>::stp_dev<true>(p + i * ZT * Pop<F16>::ES, col.b0, f[i]);
+        Pop<true>::stp_dev<NT>(p + i * ZT * Pop<F16>::ES, col.b0, f[i]);
       else
-        Pop<F16>::template stp<true>(p + i * ZT * Pop<F16>::ES, i, col.b0, f[i], 0.f);
+        Pop<F16>::template stp<NT>(p + i * ZT * Pop<F16>::ES, i, col.b0, f[i], 0.f);
     }
   }
 }
@@ -294,7 +294,7 @@ __device__ __forceinline__ void plain_block(const CollideArgs& a, int x, int zci
 // the wall model (the wall row's neighbour velocity through LDS).  Density
 // and momentum are summed directly so that the pair sums of the collision
 // are not live across the Newton solve (fewer registers).
-template <bool F16, bool REF, int ZL = ZT>
+template <bool F16, bool REF, bool NT = true, int ZL = ZT>
 __device__ __forceinline__ void wall_block(const CollideArgs& a, int x, int zci, int gy, float (*lds_u2)[2][ZL],
                                            const float* __restrict__ dref, float* lref = nullptr) {
   const int lane = threadIdx.x & (ZL - 1);
@@ -373,11 +373,11 @@ __device__ __forceinline__ void wall_block(const CollideArgs& a, int x, int zci,
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       if (F16 && REF)
-        Pop<true>::stp_dev<true>(p + i * ZT * Pop<F16>::ES, col.b0, f[i], ZL < ZT ? lref[(w + 1) * Q + i] : dref[y * Q + i]);
+        Pop<true>::stp_dev<NT>(p + i * ZT * Pop<F16>::ES, col.b0, f[i], ZL < ZT ? lref[(w + 1) * Q + i] : dref[y * Q + i]);
       else if (F16)
-        Pop<true>::stp_dev<true>(p + i * ZT * Pop<F16>::ES, col.b0, f[i]);
+        Pop<true>::stp_dev<NT>(p + i * ZT * Pop<F16>::ES, col.b0, f[i]);
       else
-        Pop<F16>::template stp<true>(p + i * ZT * Pop<F16>::ES, i, col.b0, f[i], 0.f);
+        Pop<F16>::template stp<NT>(p + i * ZT * Pop<F16>::ES, i, col.b0, f[i], 0.f);
     }
   }
 }
@@ -441,7 +441,7 @@ constexpr int FUSED_SHORT_WAVES = 6;
 // 400x40x32 24.1 -> 20.6, 64x32x32 9.9 -> 7.6, 600x60x24 32.2 -> 28.7,
 // 200x20x16 13.4 -> 10.3, 880x80x16 56.0 -> 55.1 (bound by the padded bricks'
 // 128-byte lines).
-template <bool F16, bool FORCE, bool REF, int ZL>
+template <bool F16, bool FORCE, bool REF, bool NT, int ZL>
 __global__ __launch_bounds__(YROWS* ZL) __attribute__((amdgpu_waves_per_eu(ZL == ZT ? 8 : FUSED_SHORT_WAVES)))
 void collide_fused_kernel(CollideArgs a, const int* __restrict__ gl, int n_gen, const int* __restrict__ bl,
                           const float* __restrict__ dref, const float* __restrict__ dpull) {
@@ -465,7 +465,7 @@ void collide_fused_kernel(CollideArgs a, const int* __restrict__ gl, int n_gen, 
     issue_pulls<F16, ZL == ZT>(a, g, col, r);
     float f[Q];
     convert_pulls<F16, ZL == ZT>(a, g, r, f);
-    node_update<F16, true, ZL>(a, x, y, z, lane, base, zci, owned, active, col, f, lds_u2);
+    node_update<F16, NT, ZL>(a, x, y, z, lane, base, zci, owned, active, col, f, lds_u2);
     return;
   }
   const int e = bl[b - n_gen];
@@ -475,9 +475,9 @@ void collide_fused_kernel(CollideArgs a, const int* __restrict__ gl, int n_gen, 
   const int base = min(YROWS * gy, a.ny - YROWS);
   __shared__ float lref[REF && ZL < ZT ? RowRef<ZL>::N : 1];
   if (a.ywall != LBM_Y_PERIODIC && (base == 0 || base == a.ny - YROWS))
-    wall_block<F16, REF, ZL>(a, x, zci, gy, lds_u2, dref, lref);
+    wall_block<F16, REF, NT, ZL>(a, x, zci, gy, lds_u2, dref, lref);
   else
-    plain_block<F16, FORCE, REF, ZL>(a, x, zci, gy, dref, dpull, lref);
+    plain_block<F16, FORCE, REF, NT, ZL>(a, x, zci, gy, dref, dpull, lref);
 }
 
 // Pre-force velocity (u_x, u_z) of node (x, y, z) after streaming and the
@@ -684,11 +684,10 @@ void fill_args(lbm_ctx* h, CollideArgs& a, int src, int dst) {
   a.wall_law = c.wall_law;
   a.newton_iters = c.newton_iters;
   a.stats_on = h->stats_on && h->d_stats != nullptr;
-  // FP32 population stores bypass the caches (non-temporal) unless the next
-  // step finds much of the state the last one wrote in the Infinity Cache.  (FP16 storage measured
-  // no gain from cached stores: it always stores non-temporally.)
-  a.nt_store = h->cfg.storage == LBM_STORE_F16DEV ||
-               touched_bytes(h->cfg) > NT_STORE_MIN_BYTES;
+  // Population stores bypass the caches (non-temporal) unless the next step finds
+  // much of the state the last one wrote in the Infinity Cache.
+  const int64_t touched = touched_bytes(c);
+  a.nt_store = touched > NT_STORE_MIN_BYTES || (h->split && c.nz > 32 && touched < NT_STORE_BELOW_F16);
   a.has_g = (c.g[0] != 0.0 || c.g[1] != 0.0 || c.g[2] != 0.0) ? 1 : 0;
   a.tau0 = (float)c.tau0;
   a.tau0sq = (float)(c.tau0 * c.tau0);
@@ -745,16 +744,19 @@ void launch_bulk_kernel(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
     const int ng = h->n_bnd, nt = ng + n;
     const int* gl = h->d_blist_bnd;
     if (nt == 0) return;
-    auto go = [&](auto FORCE, auto REF) {
-      constexpr bool F = FORCE.value, R = REF.value;
+    auto go = [&](auto FORCE, auto REF, auto NT) {
+      constexpr bool F = FORCE.value, R = REF.value, N = NT.value;
       if (h->cfg.nz <= 16)
-        collide_fused_kernel<true, F, R, 16><<<nt, YROWS * 16, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
+        collide_fused_kernel<true, F, R, N, 16><<<nt, YROWS * 16, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
       else if (h->cfg.nz <= 32)
-        collide_fused_kernel<true, F, R, 32><<<nt, YROWS * 32, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
+        collide_fused_kernel<true, F, R, N, 32><<<nt, YROWS * 32, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
       else
-        collide_fused_kernel<true, F, R, ZT><<<nt, BLOCK, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
+        collide_fused_kernel<true, F, R, N, ZT><<<nt, BLOCK, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
     };
-    auto ref = [&](auto FORCE) { a.dref ? go(FORCE, std::true_type{}) : go(FORCE, std::false_type{}); };
+    auto store = [&](auto FORCE, auto REF) {
+      a.nt_store ? go(FORCE, REF, std::true_type{}) : go(FORCE, REF, std::false_type{});
+    };
+    auto ref = [&](auto FORCE) { a.dref ? store(FORCE, std::true_type{}) : store(FORCE, std::false_type{}); };
     a.has_g ? ref(std::true_type{}) : ref(std::false_type{});
     return;
   }

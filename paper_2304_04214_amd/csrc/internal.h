@@ -33,15 +33,20 @@ constexpr int CHUNK_BLOCKS = 30000;
 // (74,000 blocks) 934, 192 planes 950, 128 planes 968, 64 planes 1032; on a second
 // MI355X, by this constant: 50,000 949, 74,000 953, 100,000 961, 150,000 977.
 constexpr int CHUNK_BLOCKS_F16 = 60000;
-// FP32 storage, where the 128-byte lines that the nodes of both state buffers
-// touch are together more than this: non-temporal population stores (the 256 MB
-// Infinity Cache holds too little of the state from one step to the next).  us
-// per step, non-temporal -> cached: 400x64x64 (249 MB) 44.5 -> 38.9, 480x64x64
-// (299 MB) 52.6 -> 47.8, 520x64x64 (324 MB) 56.8 -> 59.2.
+// Where the 128-byte lines that the nodes of both state buffers touch are
+// together more than this: non-temporal population stores (the 256 MB Infinity
+// Cache holds too little of the state from one step to the next).  us per step,
+// non-temporal -> cached: FP32 400x64x64 (249 MB) 44.5 -> 38.9, 480x64x64
+// (299 MB) 52.6 -> 47.8, 520x64x64 (324 MB) 56.8 -> 59.2; FP16 800x64x64
+// (249 MB) 47.5 -> 45.1, 400x40x32 20.0 -> 18.0, 600x80x10 36 -> 29.9.
 constexpr int64_t NT_STORE_MIN_BYTES = int64_t(288) << 20;
+// FP16 storage with 64-lane rows (nz > 32) also below this: the kernel is short
+// and the cached lines are written back at its end (64x64x64, periodic, 8.6 ->
+// 9.9 us with cached stores, 128x64x64 12.4 -> 12.6, 256x64x64 18.9 -> 18.7).
+constexpr int64_t NT_STORE_BELOW_F16 = int64_t(56) << 20;
 inline int64_t touched_bytes(const lbm_config& c) {
-  const int64_t line = 128, rest = 4 * (c.nz % ZT);
-  return 2 * (int64_t)Q * c.nx * c.ny * (c.nz / ZT * 4 * ZT + (rest + line - 1) / line * line);
+  const int64_t line = 128, el = c.storage == LBM_STORE_F32 ? 4 : 2;
+  return 2 * (int64_t)Q * c.nx * c.ny * (c.nz / ZT * el * ZT + (el * (c.nz % ZT) + line - 1) / line * line);
 }
 // Static device scratch of stg_inlet_fill_noalloc (per device, for the process
 // lifetime): the STG tables of one call must fit.
@@ -64,7 +69,7 @@ struct CollideArgs {
   const int* plane_of_x;  // [nx], -1 when not sampled
   int* err;
   int nx, ny, nz, zc, yg, nblocks;
-  int nt_store;           // 1: non-temporal population stores (all but small FP32 lattices)
+  int nt_store;           // 1: non-temporal population stores (all but small lattices)
   int ywall, xbc, wall_model, newton_iters, stats_on, has_g, wall_law;
   float tau0, tau0sq, smag;  // smag = 18 sqrt(2) C_s^2
   float g[3];

@@ -25,6 +25,9 @@ TOL16 = 2e-4
     ((5, 10, 1), dict(ywall="slip", xbc="inflow", wall_model=True)),
     ((5, 7, 20), dict(ywall="periodic", xbc="periodic", wall_model=False, g=(2e-5, -1e-5, 5e-6), tau0=0.53)),
     ((5, 11, 9), dict(ywall="bounceback", xbc="periodic", wall_model=True, wall_avg="line", g=(1e-5, 0.0, 0.0))),
+    # non-temporal stores with short rows, cached stores with 64-lane rows
+    ((622, 100, 3), dict(ywall="slip", xbc="inflow", wall_model=True)),
+    ((190, 64, 40), dict(ywall="slip", xbc="inflow", wall_model=True)),
 ])
 def test_fp16_fields_and_statistics_match_the_oracle(shape, kw, reference):
     print("short rows", shape, kw, reference, flush=True)
