@@ -39,6 +39,8 @@
 namespace lbm {
 namespace {
 
+constexpr int64_t NT_PULL_MIN_BYTES = int64_t(118) << 20;  // of both lambda buffers, see launch_adjoint
+
 // Moments (M v)_k of a population vector in the Appendix A.1 basis, from its
 // opposite-pair sums and differences.
 __device__ __forceinline__ void moments(const float v[Q], float m[Q]) {
@@ -183,7 +185,7 @@ struct AdjLds {
 // reference offsets of the stored rows and of the plain pulls' source rows,
 // passed as restrict kernel arguments so that their scalar loads are not
 // ordered after stores (the values of a.dref / a.dpull).
-template <bool F16, bool REF, bool PROBE = false>
+template <bool F16, bool REF, bool PROBE = false, bool NT = false>
 __device__ __forceinline__ void node_adjoint(const AdjointArgs& A, AdjLds& L, int x, int y, int z, int lane,
                                              int base, int zci, bool own, bool active, float& csb,
                                              const float* __restrict__ dref, const float* __restrict__ dpull) {
@@ -192,7 +194,7 @@ __device__ __forceinline__ void node_adjoint(const AdjointArgs& A, AdjLds& L, in
   const Col col = make_col<F16>(a, z);
   const Geo g = make_geo(a, x, y);
   typename Pop<F16>::Raw r[Q];
-  issue_pulls<F16>(a, g, col, r);
+  issue_pulls<F16, true, NT>(a, g, col, r);
   const uint32_t erow = rowpart(a, x, y) + col.c0;
   float f[Q];
   if (!F16 || !REF) {
@@ -580,7 +582,10 @@ __device__ __forceinline__ void node_adjoint(const AdjointArgs& A, AdjLds& L, in
 // (y, z) (x = nx-1), whose dL/dhist feeds its own c_x < 0 values.
 // Held to 96 VGPRs: 5 waves per SIMD instead of 4, at the cost of one spilled
 // VGPR with FP16 states and 11 with FP32 states (measured faster for both).
-template <bool F16, bool REF>
+// Bound by the memory system: a kernel of the interior blocks alone, 72 VGPRs
+// and 7 waves per SIMD, takes as long per block.  NT: the state is pulled with
+// non-temporal loads (launch_adjoint).
+template <bool F16, bool REF, bool NT>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(5)))
 void adjoint_kernel(AdjointArgs A, const int* __restrict__ blist, const float* __restrict__ dref,
                     const float* __restrict__ dpull) {
@@ -601,10 +606,10 @@ void adjoint_kernel(AdjointArgs A, const int* __restrict__ blist, const float* _
   const bool own = row_owned(a, y, gy, base);
   float csb = 0.f;
   if (open && x0 == a.nx - 2) {  // block-uniform
-    node_adjoint<F16, REF>(A, L, a.nx - 1, y, z, lane, base, zci, own, active, csb, dref, dpull);
+    node_adjoint<F16, REF, false, NT>(A, L, a.nx - 1, y, z, lane, base, zci, own, active, csb, dref, dpull);
     __syncthreads();  // LDS reuse by the second node
   }
-  node_adjoint<F16, REF>(A, L, x0, y, z, lane, base, zci, own, active, csb, dref, dpull);
+  node_adjoint<F16, REF, false, NT>(A, L, x0, y, z, lane, base, zci, own, active, csb, dref, dpull);
   // dL/dC_s of the block (fixed-order FP64 reduction)
   double c = (double)csb;
 #pragma unroll
@@ -744,12 +749,28 @@ hipError_t launch_adjoint(lbm_ctx* h, const AdjointArgs& args, int storage_f16, 
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if ((e = adjoint_list(h)) != hipSuccess) return e;
+  // A step reads its state once and no step soon again; the lambda it writes is
+  // the next one's input.  Where the two lambda buffers are much of the Infinity
+  // Cache the state is loaded non-temporally, so that it does not push them out:
+  // us per step 400x64x64 72.3 -> 63.2, 256x64x64 44.8 -> 43.1, 200x64x64 (125 MB
+  // of lambda) 37.9 -> 36.0, with FP16 states 35.4 -> 35.1, but 180x64x64 with FP16
+  // states (112 MB) 32.0 -> 32.8, 128x64x64 25.4 -> 26.2.
+  lbm_config lam = h->cfg;
+  lam.storage = LBM_STORE_F32;
+  const bool nt = touched_bytes(lam) > NT_PULL_MIN_BYTES;
+  auto go = [&](auto F16, auto REF, const float* dref, const float* dpull) {
+    constexpr bool F = F16.value, R = REF.value;
+    if (nt)
+      adjoint_kernel<F, R, true><<<h->n_ablist, BLOCK, 0, h->stream>>>(A, h->d_ablist, dref, dpull);
+    else
+      adjoint_kernel<F, R, false><<<h->n_ablist, BLOCK, 0, h->stream>>>(A, h->d_ablist, dref, dpull);
+  };
   if (storage_f16 && A.c.dref)
-    adjoint_kernel<true, true><<<h->n_ablist, BLOCK, 0, h->stream>>>(A, h->d_ablist, A.c.dref, A.c.dpull);
+    go(std::true_type{}, std::true_type{}, A.c.dref, A.c.dpull);
   else if (storage_f16)
-    adjoint_kernel<true, false><<<h->n_ablist, BLOCK, 0, h->stream>>>(A, h->d_ablist, nullptr, nullptr);
+    go(std::true_type{}, std::false_type{}, nullptr, nullptr);
   else
-    adjoint_kernel<false, false><<<h->n_ablist, BLOCK, 0, h->stream>>>(A, h->d_ablist, nullptr, nullptr);
+    go(std::false_type{}, std::false_type{}, nullptr, nullptr);
   return hipGetLastError();
 }
 

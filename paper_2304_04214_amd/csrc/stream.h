@@ -29,7 +29,9 @@ template <>
 struct Pop<false> {
   static constexpr uint32_t ES = 4;
   using Raw = float;
+  template <bool NT = false>  // NT: non-temporal load
   __device__ static __forceinline__ Raw raw(const char* p, uint32_t off) {
+    if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const float*>(p + off));
     return *reinterpret_cast<const float*>(p + off);
   }
   __device__ static __forceinline__ float cvt(int, Raw r, float) { return r; }
@@ -56,7 +58,9 @@ template <>
 struct Pop<true> {
   static constexpr uint32_t ES = 2;
   using Raw = uint32_t;  // the 16-bit pattern of h_i
+  template <bool NT = false>
   __device__ static __forceinline__ Raw raw(const char* p, uint32_t off) {
+    if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const unsigned short*>(p + off));
     return *reinterpret_cast<const unsigned short*>(p + off);
   }
   __device__ static __forceinline__ float cvt(int i, Raw r, float ref) {
@@ -215,14 +219,15 @@ __device__ __forceinline__ bool interior(const Geo& g) {
 // so that they can be in flight while another row is being collided.
 // UNIFORM: the row is the same in every lane of a wave (otherwise the shorter
 // code of interior rows would come on top of the general one).
-template <bool F16, bool UNIFORM = true>
+// NT: the state is read this once (non-temporal loads).
+template <bool F16, bool UNIFORM = true, bool NT = false>
 __device__ __forceinline__ void issue_pulls(const CollideArgs& a, const Geo& g, const Col& col,
                                             typename Pop<F16>::Raw r[Q]) {
   if (UNIFORM && interior(g)) {
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
       const uint32_t cs = CZ[i] == 1 ? col.bm : (CZ[i] == -1 ? col.bp : col.b0);
-      r[i] = Pop<F16>::raw(row_ptr<F16>(a.src, rowpart(a, g.xs[CX[i] + 1], g.ys[CY[i] + 1]) + (uint32_t)i * ZT), cs);
+      r[i] = Pop<F16>::template raw<NT>(row_ptr<F16>(a.src, rowpart(a, g.xs[CX[i] + 1], g.ys[CY[i] + 1]) + (uint32_t)i * ZT), cs);
     }
   } else {
 #pragma unroll
@@ -239,7 +244,7 @@ __device__ __forceinline__ void issue_pulls(const CollideArgs& a, const Geo& g, 
         ysrc = out ? g.y : ysrc;
         csrc = bb ? col.b0 : cs;
       }
-      r[i] = Pop<F16>::raw(row_ptr<F16>(a.src, rowpart(a, xsrc, ysrc) + (uint32_t)plane * ZT), csrc);
+      r[i] = Pop<F16>::template raw<NT>(row_ptr<F16>(a.src, rowpart(a, xsrc, ysrc) + (uint32_t)plane * ZT), csrc);
     }
   }
 }
