@@ -37,6 +37,28 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// v of the lane N places on in its 16 lanes.
+template <int N>
+__device__ __forceinline__ double rotate16(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  constexpr int ROW_ROR = 0x120;
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, ROW_ROR + N, 0xf, 0xf, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), ROW_ROR + N, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// Sum over each 16 (or 32) lanes: the additions of wave_sum, whose other operands
+// are zero.  After the step of 8 the lanes repeat with period 8, and so on, so
+// that rotations give what lane ^ 8, ^ 4, ^ 2, ^ 1 hold.
+__device__ __forceinline__ double row_sum(double v, bool of32) {
+  if (of32) v += __shfl_xor(v, 16, ZT);  // wave-uniform
+  v += rotate16<8>(v);
+  v += rotate16<4>(v);
+  v += rotate16<2>(v);
+  v += rotate16<1>(v);
+  return v;
+}
+
 // rb rows of one x-plane a block, `groups` blocks a plane, the planes x0 ..
 // x0 + planes - 1.  The stores go through the caches: blocks end within rows,
 // and lines written in parts bypassing the caches cost more than what the next
@@ -98,6 +120,12 @@ __global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int x
 #pragma unroll
     for (int k = 0; k < 3; ++k) e0[k] = a.u_in[k * a.ny * a.nz + pz];
   }
+  // a sampled plane: this wave's first rows q1 .., their lanes, and what was summed so far
+  const int sample = a.stats_on ? plane_of_x[x] : -1;
+  const int lanes = a.nz <= 16 ? 16 : 32, per = ZT / lanes, zl = t & (lanes - 1);
+  const int q1 = rb * gy - base + uni(t >> 6) * per, qt = q1 + (t & (ZT - 1)) / lanes;
+  double* const stat = a.stats + ((size_t)max(sample, 0) * a.ny + base) * 9 + zl;
+  const double before = sample >= 0 && qt < rb && zl < 9 ? stat[9 * qt] : 0.0;
   float f[Q];
 #pragma unroll
   for (int i = 0; i < Q; ++i) f[i] = pull(x, gx.xs[CX[i] + 1], i);
@@ -167,34 +195,38 @@ __global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int x
     for (int i = 0; i < Q; ++i) Pop<false>::stp<false>(d + i * (ZT * 4), i, self, f[i], 0.f);
   }
 
-  // ---- statistics: sums over z (nz <= 32, so one wave holds a row) of the block's own rows ----
+  // ---- statistics: sums over z of the block's own rows ----
+  // A wave takes as many rows at a time as have 16 or 32 lanes each, and nine lanes
+  // add the nine sums of a row: row after row, and one sum after the other, the
+  // sampled blocks were the launch's tail (62x22x9 with twelve planes 22.6 us per
+  // step, now 7.6; 200x20x16 18.0, now 7.8).
   const int lane = t & (ZT - 1), wave = uni(t >> 6), nw = blockDim.x / ZT;
-  const bool on = lane < a.nz;
-  if (a.stats_on) {
-    const int p = plane_of_x[x];
-    if (p >= 0) {  // block-uniform
-      L.u[0][t] = ux;
-      L.u[1][t] = uy;
-      L.u[2][t] = uz;
-      __syncthreads();
-      for (int q = rb * gy - base + wave; q < rb; q += nw) {
-        const int k0 = q * a.nz + (on ? lane : 0);
-        const double dx = L.u[0][k0], dy = L.u[1][k0], dz = L.u[2][k0];
-        const double v[9] = {dx, dy, dz, dx * dx, dy * dy, dz * dz, dx * dy, dx * dz, dy * dz};
-        double* s = a.stats + ((size_t)p * a.ny + base + q) * 9;
+  if (sample >= 0) {  // block-uniform
+    L.u[0][t] = ux;
+    L.u[1][t] = uy;
+    L.u[2][t] = uz;
+    __syncthreads();
+    for (int q0 = q1; q0 < rb; q0 += nw * per) {
+      const int q = min(q0 + lane / lanes, rb - 1);
+      const bool row = q == q0 + lane / lanes, node = row && zl < a.nz, out = row && zl < 9;
+      const double s = q0 == q1 ? before : (out ? stat[9 * q] : 0.0);
+      const int k0 = q * a.nz + (node ? zl : 0);
+      const double dx = L.u[0][k0], dy = L.u[1][k0], dz = L.u[2][k0];
+      const double v[9] = {dx, dy, dz, dx * dx, dy * dy, dz * dz, dx * dy, dx * dz, dy * dz};
+      double mine9 = 0.0;
 #pragma unroll
-        for (int k = 0; k < 9; ++k) {
-          const double sum = wave_sum(on ? v[k] : 0.0);
-          if (lane == 0) s[k] += sum;
-        }
+      for (int k = 0; k < 9; ++k) {
+        const double sum = row_sum(node ? v[k] : 0.0, lanes == 32);
+        mine9 = zl == k ? sum : mine9;
       }
+      if (out) stat[9 * q] = s + mine9;
     }
   }
   if (wblock && a.wall_acc) {  // block-uniform: sums of u_tau, by the blocks that own a wall row
     __syncthreads();
     for (int w = wave; w < 2; w += nw) {
       if (w == 0 ? gy != 0 : gy != groups - 1) continue;
-      const double sum = wave_sum(on ? (double)L.ut[w][lane] : 0.0);
+      const double sum = wave_sum(lane < a.nz ? (double)L.ut[w][lane] : 0.0);
       if (lane == 0) a.wall_acc[(size_t)w * a.nx + x] += sum;
     }
   }
@@ -208,8 +240,8 @@ __global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int x
 // (60,000 rows) 58.5 -> 48.3, 687x104x28 (71,000) 65 -> 108, with non-temporal
 // stores 82.  Beyond 32 a row leaves less than half the wave idle and little is
 // won by more nodes a wave (190x63x48 18.3 -> 18.4, 400x75x40 42.5 -> 46.5).
-// The rows are those that
-// leave the fewest threads without a row of their own.  Up to 2^17 nodes the
+// The rows are those that leave the fewest threads without a row of their own.
+// Up to 2^17 nodes the
 // chip takes all blocks in one round and the smallest such blocks are taken
 // (200x20x16: 6.5 us per step with one wave a block, 7.4 with two of which a
 // quarter idles); above, the largest of up to 256 threads (400x40x32 15.3 us,
