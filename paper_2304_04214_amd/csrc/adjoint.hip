@@ -39,7 +39,8 @@
 namespace lbm {
 namespace {
 
-constexpr int64_t NT_PULL_MIN_BYTES = int64_t(118) << 20;  // of both lambda buffers, see launch_adjoint
+// of both lambda buffers, see launch_adjoint
+constexpr int64_t NT_PULL_MIN_BYTES = int64_t(118) << 20, NT_PULL_MAX_BYTES = int64_t(320) << 20;
 
 // Moments (M v)_k of a population vector in the Appendix A.1 basis, from its
 // opposite-pair sums and differences.
@@ -754,10 +755,11 @@ hipError_t launch_adjoint(lbm_ctx* h, const AdjointArgs& args, int storage_f16, 
   // Cache the state is loaded non-temporally, so that it does not push them out:
   // us per step 400x64x64 72.3 -> 63.2, 256x64x64 44.8 -> 43.1, 200x64x64 (125 MB
   // of lambda) 37.9 -> 36.0, with FP16 states 35.4 -> 35.1, but 180x64x64 with FP16
-  // states (112 MB) 32.0 -> 32.8, 128x64x64 25.4 -> 26.2.
+  // states (112 MB) 32.0 -> 32.8, 128x64x64 25.4 -> 26.2.  Lambda buffers larger than the
+  // cache are not kept in any case (189x127x116, 468 MB, 159 -> 169).
   lbm_config lam = h->cfg;
   lam.storage = LBM_STORE_F32;
-  const bool nt = touched_bytes(lam) > NT_PULL_MIN_BYTES;
+  const bool nt = touched_bytes(lam) > NT_PULL_MIN_BYTES && touched_bytes(lam) < NT_PULL_MAX_BYTES;
   auto go = [&](auto F16, auto REF, const float* dref, const float* dpull) {
     constexpr bool F = F16.value, R = REF.value;
     if (nt)
