@@ -756,10 +756,13 @@ hipError_t launch_adjoint(lbm_ctx* h, const AdjointArgs& args, int storage_f16, 
   // us per step 400x64x64 72.3 -> 63.2, 256x64x64 44.8 -> 43.1, 200x64x64 (125 MB
   // of lambda) 37.9 -> 36.0, with FP16 states 35.4 -> 35.1, but 180x64x64 with FP16
   // states (112 MB) 32.0 -> 32.8, 128x64x64 25.4 -> 26.2.  Lambda buffers larger than the
-  // cache are not kept in any case (189x127x116, 468 MB, 159 -> 169).
+  // cache are not kept in any case (189x127x116, 468 MB, 159 -> 169); with more
+  // than two bricks a row the lines that neighbouring bricks share are read again
+  // (80x68x279 66 -> 68).
   lbm_config lam = h->cfg;
   lam.storage = LBM_STORE_F32;
-  const bool nt = touched_bytes(lam) > NT_PULL_MIN_BYTES && touched_bytes(lam) < NT_PULL_MAX_BYTES;
+  const bool nt = touched_bytes(lam) > NT_PULL_MIN_BYTES && touched_bytes(lam) < NT_PULL_MAX_BYTES &&
+                  lam.nz <= 2 * ZT;
   auto go = [&](auto F16, auto REF, const float* dref, const float* dpull) {
     constexpr bool F = F16.value, R = REF.value;
     if (nt)

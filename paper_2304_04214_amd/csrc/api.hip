@@ -327,8 +327,11 @@ hipError_t enqueue_steps(lbm_ctx* h, int cur, int64_t time, int32_t nsteps, hipS
                                      n + nb == nsteps ? nb - 1 : -1);
       if (e != hipSuccess) return e;
     }
-    if (h->split && (e = lbm::launch_boundary(h, cur, 1 - cur, st, ring)) != hipSuccess) return e;
-    if ((e = timed_launch(h, cur, 1 - cur, ring, st)) != hipSuccess) return e;
+    h->last_step = n == nsteps - 1;
+    if (h->split) e = lbm::launch_boundary(h, cur, 1 - cur, st, ring);
+    if (!h->split || e == hipSuccess) e = timed_launch(h, cur, 1 - cur, ring, st);
+    h->last_step = false;
+    if (e != hipSuccess) return e;
     cur = 1 - cur;
   }
   return hipSuccess;

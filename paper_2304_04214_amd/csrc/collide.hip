@@ -687,7 +687,8 @@ void fill_args(lbm_ctx* h, CollideArgs& a, int src, int dst) {
   // Population stores bypass the caches (non-temporal) unless the next step finds
   // much of the state the last one wrote in the Infinity Cache.
   const int64_t touched = touched_bytes(c);
-  a.nt_store = touched > NT_STORE_MIN_BYTES || (h->split && c.nz > 32 && touched < NT_STORE_BELOW_F16);
+  a.nt_store = touched > NT_STORE_MIN_BYTES || (h->split && c.nz > 32 && touched < NT_STORE_BELOW_F16) ||
+               (h->last_step && touched > NT_LAST_MIN_BYTES[h->split]);
   a.has_g = (c.g[0] != 0.0 || c.g[1] != 0.0 || c.g[2] != 0.0) ? 1 : 0;
   a.tau0 = (float)c.tau0;
   a.tau0sq = (float)(c.tau0 * c.tau0);

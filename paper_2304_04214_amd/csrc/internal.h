@@ -44,6 +44,11 @@ constexpr int64_t NT_STORE_MIN_BYTES = int64_t(288) << 20;
 // and the cached lines are written back at its end (64x64x64, periodic, 8.6 ->
 // 9.9 us with cached stores, 128x64x64 12.4 -> 12.6, 256x64x64 18.9 -> 18.7).
 constexpr int64_t NT_STORE_BELOW_F16 = int64_t(56) << 20;
+// Above this (FP32, FP16) a call's last step stores non-temporally: the next call
+// may be for another state, and lines then only written back cost (calls of two
+// steps on states in turn, FP16 99x107x227 97 -> 89 us a call, 320x128x24 112 ->
+// 106, FP32 743x17x100 three steps 167 -> 160).
+constexpr int64_t NT_LAST_MIN_BYTES[2] = {int64_t(192) << 20, int64_t(64) << 20};
 inline int64_t touched_bytes(const lbm_config& c) {
   const int64_t line = 128, el = c.storage == LBM_STORE_F32 ? 4 : 2;
   return 2 * (int64_t)Q * c.nx * c.ny * (c.nz / ZT * el * ZT + (el * (c.nz % ZT) + line - 1) / line * line);
@@ -173,6 +178,7 @@ struct lbm_ctx {
   float* d_fl_ring = nullptr;   // the same for a v', when the bound STG inputs keep it
   int* d_ablist = nullptr;      // [n_ablist] adjoint block entries in dispatch order (-1 pads)
   int n_ablist = 0;
+  bool last_step = false;       // the step being enqueued is its call's last
   int timing = 0;
   std::vector<hipEvent_t> ev;  // pairs (start, stop) of timed launches
   int64_t ev_used = 0;
