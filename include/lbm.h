@@ -253,8 +253,9 @@ lbm_status stg_inlet_fill_noalloc(lbm_handle h, const lbm_stg* stg, double t);
  * from the inlet, outlet and statistics planes (wall rows included) run in a
  * lean kernel, one dispatch per range of x-planes, after a general kernel for
  * the other blocks (one fused launch on lattices of up to 2^24 nodes); with
- * LBM_STORE_F32 the general kernel covers all blocks, one dispatch per range of
- * x-planes (lbm_collide_dispatches).
+ * LBM_STORE_F32 the general kernel (on lattices of nz <= 32 that stay in the
+ * caches the row kernel, with equal results) covers all blocks, one dispatch per
+ * range of x-planes (lbm_collide_dispatches).
  * stg: bound when non-NULL; required (now or earlier) with LBM_X_INFLOW.
  * Asynchronous on the handle's stream.
  */

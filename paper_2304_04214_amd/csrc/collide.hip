@@ -685,7 +685,8 @@ void fill_args(lbm_ctx* h, CollideArgs& a, int src, int dst) {
   a.newton_iters = c.newton_iters;
   a.stats_on = h->stats_on && h->d_stats != nullptr;
   // Population stores bypass the caches (non-temporal) unless the next step finds
-  // much of the state the last one wrote in the Infinity Cache.
+  // much of the state the last one wrote in the Infinity Cache (the limits are at
+  // their constants).
   const int64_t touched = touched_bytes(c);
   a.nt_store = touched > NT_STORE_MIN_BYTES || (h->split && c.nz > 32 && touched < NT_STORE_BELOW_F16) ||
                (h->last_step && touched > NT_LAST_MIN_BYTES[h->split]);

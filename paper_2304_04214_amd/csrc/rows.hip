@@ -241,12 +241,11 @@ __global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int x
 // stores 82.  Beyond 32 a row leaves less than half the wave idle and little is
 // won by more nodes a wave (190x63x48 18.3 -> 18.4, 400x75x40 42.5 -> 46.5).
 // The rows are those that leave the fewest threads without a row of their own.
-// Up to 2^17 nodes the
-// chip takes all blocks in one round and the smallest such blocks are taken
-// (200x20x16: 6.5 us per step with one wave a block, 7.4 with two of which a
-// quarter idles); above, the largest of up to 256 threads (400x40x32 15.3 us,
-// 16.9 with 128).  Every block has at least two rows, a wall row and the row
-// next to it.
+// Up to 2^17 nodes the chip takes all blocks in one round and the smallest such
+// blocks are taken (200x20x16: 6.5 us per step with one wave a block, 7.4 with two
+// of which a quarter idles); above, the largest of up to 256 threads (400x40x32
+// 15.3 us, 16.9 with 128).  Every block has at least two rows, a wall row and the
+// row next to it.
 void plan_rows(lbm_ctx* h) {
   const lbm_config& c = h->cfg;
   h->rows = 0;
