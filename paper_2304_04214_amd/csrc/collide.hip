@@ -786,7 +786,7 @@ void launch_bulk_kernel(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
 void launch_edge_kernels(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
   const bool f16 = h->cfg.storage == LBM_STORE_F16DEV;
   if (h->rows) {
-    (void)launch_rows(h, a, stream);  // all blocks; the caller reads the launch's error
+    launch_rows(h, a, stream);  // all blocks
     return;
   }
   for (size_t k = 0; k + 1 < h->bnd_off.size(); ++k) {

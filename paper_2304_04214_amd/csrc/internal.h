@@ -208,7 +208,7 @@ hipError_t launch_field_export(lbm_ctx* h, const float* bricks, float* soa);
 hipError_t launch_field_import(lbm_ctx* h, const float* soa, float* bricks);
 // rows.hip
 void plan_rows(lbm_ctx* h);
-hipError_t launch_rows(lbm_ctx* h, const CollideArgs& a, hipStream_t stream);
+void launch_rows(lbm_ctx* h, const CollideArgs& a, hipStream_t stream);
 // adjoint.hip
 hipError_t launch_adjoint(lbm_ctx* h, const AdjointArgs& args, int storage_f16, double t_next, bool fill_inlet,
                           float* u_in, float* fluct);

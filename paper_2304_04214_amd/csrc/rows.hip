@@ -264,15 +264,15 @@ void plan_rows(lbm_ctx* h) {
   }
 }
 
-// One dispatch per x-range, as the general kernel.
-hipError_t launch_rows(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
+// One dispatch per x-range, as the general kernel.  The caller reads the launch error:
+// reading clears it.
+void launch_rows(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
   const dim3 block(h->row_threads);
   for (int x0 = 0; x0 < h->cfg.nx; x0 += h->chunk_planes) {
     const int planes = std::min(h->chunk_planes, h->cfg.nx - x0);
     const dim3 grid((unsigned)planes * h->row_groups);
     collide_rows_kernel<<<grid, block, 0, stream>>>(a, x0, planes, h->rows, h->row_groups, a.plane_of_x);
   }
-  return hipGetLastError();
 }
 
 }  // namespace lbm
