@@ -382,10 +382,13 @@ lbm_status lbm_step_record(lbm_handle h, const lbm_stg* stg, const void* s_start
  * current one on return.  uin_keep[k] and fluct_keep[k] receive the inlet
  * plane that step k used; the last one's also goes to the bound u_in / fluct.
  * Host arrays of nsteps - 1 (f_keep, hist_keep) and nsteps device pointers,
- * buffers as for lbm_create / lbm_stg, none of them the handle's own and
- * consecutive ones different; hist_keep, uin_keep and fluct_keep are required
+ * buffers as for lbm_create / lbm_stg, none of them the handle's own or the
+ * bound u_in / fluct, consecutive ones different, uin_keep[k] and fluct_keep[k]
+ * apart (a buffer given for several steps holds the last one's); hist_keep,
+ * uin_keep and fluct_keep are required
  * with LBM_X_INFLOW and not read without.  Statistics accumulate as in
- * lbm_step.  Errors: as lbm_step, LBM_ERR_SHAPE (alignment of f_keep).
+ * lbm_step.  Errors: as lbm_step, LBM_ERR_ARG (NULL or aliasing buffers),
+ * LBM_ERR_SHAPE (alignment of f_keep).
  */
 lbm_status lbm_step_keep(lbm_handle h, const lbm_stg* stg, int32_t nsteps, void* const* f_keep,
                          float* const* hist_keep, float* const* uin_keep, float* const* fluct_keep);

@@ -93,6 +93,27 @@ void free_tables(lbm_ctx* h) {
   t = lbm::StgTables();
 }
 
+bool overlap(const void* p, const void* q, size_t bytes) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+  return (a > b ? a - b : b - a) < bytes;
+}
+
+size_t plane_bytes(const lbm_ctx* h) { return sizeof(float) * 3 * (size_t)h->cfg.ny * h->cfg.nz; }
+
+// How many of the inlet planes from step k on one launch may fill: up to
+// STG_BATCH, as far as no plane takes memory of an earlier one, which that
+// one's step, running after the launch, still reads.
+int plane_batch(const lbm_ctx* h, int32_t k, int32_t nsteps, float* const* u, float* const* f) {
+  const size_t bytes = plane_bytes(h);
+  const int most = (int)std::min<int64_t>(lbm::STG_BATCH, nsteps - k);
+  for (int j = 1; j < most; ++j)
+    for (int i = 0; i < j; ++i)
+      if (overlap(u[k + j], u[k + i], bytes) || overlap(f[k + j], f[k + i], bytes) ||
+          overlap(u[k + j], f[k + i], bytes) || overlap(f[k + j], u[k + i], bytes))
+        return j;
+  return most;
+}
+
 // The timed collide launch (the bulk kernel with FP16 storage, or the fused
 // kernel on small lattices; with FP32 storage the general kernel's dispatches
 // over the step's x-chunks), bracketed by events when enabled.
@@ -348,9 +369,11 @@ static hipError_t enqueue_kept(lbm_ctx* h, int32_t nsteps, void* const* f_keep, 
   void* src = h->f[h->cur];
   float* hsrc = h->hist[h->cur];
   hipError_t e;
+  int32_t filled = 0;  // steps whose inlet planes have been launched
   for (int32_t n = 0; n < nsteps; ++n) {
-    if (inflow && n % lbm::STG_BATCH == 0) {
-      const int nb = (int)std::min<int64_t>(lbm::STG_BATCH, nsteps - n);
+    if (inflow && n == filled) {
+      const int nb = plane_batch(h, n, nsteps, uin_keep, fluct_keep);
+      filled += nb;
       lbm::PlaneDst dst{};
       for (int j = 0; j < nb; ++j) {
         dst.u[j] = uin_keep[n + j];
@@ -370,7 +393,7 @@ static hipError_t enqueue_kept(lbm_ctx* h, int32_t nsteps, void* const* f_keep, 
     hsrc = h->hist[1];
   }
   if (!inflow) return hipSuccess;
-  const size_t bytes = sizeof(float) * 3 * (size_t)h->cfg.ny * h->cfg.nz;
+  const size_t bytes = plane_bytes(h);
   e = hipMemcpyAsync(h->stg.u_in, uin_keep[nsteps - 1], bytes, hipMemcpyDeviceToDevice, h->stream);
   if (e != hipSuccess || !h->stg.fluct) return e;
   return hipMemcpyAsync(h->stg.fluct, fluct_keep[nsteps - 1], bytes, hipMemcpyDeviceToDevice, h->stream);
@@ -551,12 +574,14 @@ lbm_status lbm_step_record(lbm_handle h, const lbm_stg* stg, const void* s_start
   // with every plane kept, the planes of up to STG_BATCH steps come from one launch
   bool batch = inflow && uin_out && fluct_out;
   for (int32_t k = 0; batch && k < nsteps; ++k) batch = fluct_out[k] != nullptr;
+  int32_t filled = 0;
   for (int32_t k = 0; k < nsteps; ++k) {
     const void* src = k == 0 ? s_start : f_out[k - 1];
     float* uin = uin_out ? uin_out[k] : h->stg.u_in;
     float* fl = fluct_out ? fluct_out[k] : nullptr;
-    if (batch && k % lbm::STG_BATCH == 0) {
-      const int nb = (int)std::min<int64_t>(lbm::STG_BATCH, nsteps - k);
+    if (batch && k == filled) {
+      const int nb = plane_batch(h, k, nsteps, uin_out, fluct_out);
+      filled += nb;
       lbm::PlaneDst dst{};
       for (int j = 0; j < nb; ++j) {
         dst.u[j] = uin_out[k + j];
@@ -578,8 +603,17 @@ lbm_status lbm_step_keep(lbm_handle h, const lbm_stg* stg, int32_t nsteps, void*
   if (!h || nsteps < 0 || (nsteps > 1 && !f_keep)) return LBM_ERR_ARG;
   const bool inflow = h->cfg.xbc == LBM_X_INFLOW;
   if (inflow && ((nsteps > 1 && !hist_keep) || (nsteps > 0 && (!uin_keep || !fluct_keep)))) return LBM_ERR_ARG;
+  const lbm_stg* const bound = stg ? stg : (h->stg_bound ? &h->stg : nullptr);
   for (int32_t k = 0; k < nsteps; ++k) {
-    if (inflow && (!uin_keep[k] || !fluct_keep[k])) return LBM_ERR_ARG;
+    if (inflow) {
+      const size_t bytes = plane_bytes(h);
+      float* const u = uin_keep[k];
+      float* const f = fluct_keep[k];
+      if (!u || !f || overlap(u, f, bytes)) return LBM_ERR_ARG;
+      if (k > 0 && (u == uin_keep[k - 1] || f == fluct_keep[k - 1])) return LBM_ERR_ARG;
+      for (const float* b : {bound ? bound->u_in : nullptr, bound ? bound->fluct : nullptr})
+        if (b && (overlap(u, b, bytes) || overlap(f, b, bytes))) return LBM_ERR_ARG;
+    }
     if (k == nsteps - 1) break;
     if (!f_keep[k] || f_keep[k] == h->f[0] || f_keep[k] == h->f[1] || (k > 0 && f_keep[k] == f_keep[k - 1]))
       return LBM_ERR_ARG;
