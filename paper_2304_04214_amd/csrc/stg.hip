@@ -138,6 +138,18 @@ __global__ __launch_bounds__(256) void stg_spectrum_kernel(lbm_stg s, float* row
   if (bad) atomicOr(err, ERRBIT_STG_TABLE);
 }
 
+// A phase of so many turns that cos_sin would not count them exactly, and the
+// phase without them: fewer by multiples of 2^s 2 pi, about 50 bits at a time,
+// each count and fused multiply-add exact.
+__device__ __forceinline__ bool far_phase(double ph) { return !(fabs(ph) < 0x1p52); }
+__device__ __forceinline__ double nearer(double ph) {
+  while (far_phase(ph) && fabs(ph) < HUGE_VAL) {
+    const int s = ilogb(ph) - 50;
+    ph = fma(-trunc(ldexp(ph, -s) * (1.0 / TWO_PI)), ldexp(TWO_PI, s), ph);
+  }
+  return ph;
+}
+
 // cos and sin of ph in FP64: reduced by multiples of 2 pi (as fmod does: the
 // fused multiply-add is exact) and then of pi / 2, and the Taylor polynomials
 // of degree 16 and 17 on |x| <= pi / 4 (remainders below 1e-17).  About 40
@@ -197,6 +209,7 @@ __global__ __launch_bounds__(256) void stg_fill_kernel(lbm_stg s, StgTables t, i
   const int j = blockIdx.z;
   const double time = time0 + j;
   // (y, t)-dependent phase of every mode, FP64 reduced to [0, 2 pi); rows beyond the last repeat it
+  bool far = false;
   for (int n = threadIdx.x; n < N; n += 256) {
     const double ky = t.ky[n], ot = s.omega[n], phi = s.phi[n];
     const float a0 = t.amp3[n], a1 = t.amp3[N + n], a2 = t.amp3[2 * N + n];
@@ -211,6 +224,16 @@ __global__ __launch_bounds__(256) void stg_fill_kernel(lbm_stg s, StgTables t, i
       }
     }
     if (!ROWAMP) amp[n] = make_float4(a0, a1, a2, 0.f);
+    far |= far_phase(fabs(ky) * ny + fabs(ot * time) + fabs(phi));  // no row's phase is larger
+  }
+  if (far) {  // once more, apart: within the loop above it takes registers from the kernel
+#pragma unroll 1
+    for (int n = threadIdx.x; n < N; n += 256)
+#pragma unroll 1
+      for (int k = 0; k < RB; ++k) {
+        const double2 cs = cos_sin(nearer(t.ky[n] * (min(y0 + k, ny - 1) + 0.5) + s.omega[n] * time + s.phi[n]));
+        rowph[k * N + n] = make_float2((float)cs.x, (float)cs.y);
+      }
   }
   __syncthreads();
   float v[RB][3] = {};
