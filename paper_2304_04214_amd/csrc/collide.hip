@@ -762,22 +762,23 @@ void launch_bulk_kernel(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
     a.has_g ? ref(std::true_type{}) : ref(std::false_type{});
     return;
   }
-  // one dispatch per x-chunk of the list (see CHUNK_BLOCKS_F16)
+  if (n == 0) return;
+  // With reference offsets one dispatch over the list, without them one per
+  // x-chunk of it (see CHUNK_BLOCKS_F16).
+  if (a.dref) {
+    if (a.has_g)
+      collide_bulk_kernel<true, true, true><<<n, BLOCK, 0, stream>>>(a, bl, a.dref, a.dpull);
+    else
+      collide_bulk_kernel<true, false, true><<<n, BLOCK, 0, stream>>>(a, bl, a.dref, a.dpull);
+    return;
+  }
   for (size_t k = 0; k + 1 < h->int_off.size(); ++k) {
     const int m = h->int_off[k + 1] - h->int_off[k];
     const int* bk = bl + h->int_off[k];
-    if (m <= 0) continue;
-    if (a.dref) {
-      if (a.has_g)
-        collide_bulk_kernel<true, true, true><<<m, BLOCK, 0, stream>>>(a, bk, a.dref, a.dpull);
-      else
-        collide_bulk_kernel<true, false, true><<<m, BLOCK, 0, stream>>>(a, bk, a.dref, a.dpull);
-    } else {
-      if (a.has_g)
-        collide_bulk_kernel<true, true, false><<<m, BLOCK, 0, stream>>>(a, bk, a.dref, a.dpull);
-      else
-        collide_bulk_kernel<true, false, false><<<m, BLOCK, 0, stream>>>(a, bk, a.dref, a.dpull);
-    }
+    if (a.has_g)
+      collide_bulk_kernel<true, true, false><<<m, BLOCK, 0, stream>>>(a, bk, nullptr, nullptr);
+    else
+      collide_bulk_kernel<true, false, false><<<m, BLOCK, 0, stream>>>(a, bk, nullptr, nullptr);
   }
 }
 

@@ -28,10 +28,14 @@ constexpr int64_t FUSED_MAX_NODES = int64_t(1) << 24;  // FP16: one fused collid
 // dispatch over all blocks reaches 0.69-0.70; the FP16 bulk kernel has
 // its own number below.
 constexpr int CHUNK_BLOCKS = 30000;
-// FP16 storage: the bulk kernel's blocks likewise, in dispatches of about this
-// many.  1536x128x384, us per step where one dispatch takes 980: 384 planes
-// (74,000 blocks) 934, 192 planes 950, 128 planes 968, 64 planes 1032; on a second
-// MI355X, by this constant: 50,000 949, 74,000 953, 100,000 961, 150,000 977.
+// FP16 storage without reference offsets: the bulk kernel's blocks likewise, in
+// dispatches of about this many.  A gain of about 1% and fewer slow calls, us per
+// four steps with one dispatch -> with these: 1536x192x384 5793 -> 5689,
+// 1536x256x384 7606 -> 7548, 3072x64x384 3981 -> 3933, 1101x120x261 2213 -> 2138,
+// 1536x128x384 3824 -> 3833 (on other boxes 980 -> 934 to 953 a step; 64 planes a
+// dispatch 1032).  With reference offsets every range loses (1536x256x384 7891 ->
+// 8014, 1536x192x384 5983 -> 6038, 1101x120x261 2207 -> 2230, 1536x128x384 4035 ->
+// 4069) and the step keeps one dispatch.
 constexpr int CHUNK_BLOCKS_F16 = 60000;
 // Where the 128-byte lines that the nodes of both state buffers touch are
 // together more than this: non-temporal population stores (the 256 MB Infinity

@@ -39,7 +39,7 @@ class Runtime:
     """The double, the library bound to it, and the record of launches and calls."""
 
     def __init__(self):
-        self.launches = []  # (kernel, grid, threads)
+        self.launches = []  # (kernel, grid, threads, template arguments)
         self.calls = []     # (name, dst, src, bytes)
         self.fail = lambda kernel: False
         self.on_launch = lambda kernel, args: None
@@ -52,7 +52,9 @@ class Runtime:
     def _launch(self, name, gx, gy, gz, threads, args):
         kernel = re.search(r"(?<=\d)([a-z][a-z0-9_]*_kernel)", name.decode())
         kernel = kernel.group(1) if kernel else name.decode()
-        self.launches.append((kernel, (gx, gy, gz), threads))
+        targs = re.search("_kernelI((?:L[bi][0-9]+E)+)E", name.decode())
+        targs = [int(v) for v in re.findall("L[bi]([0-9]+)E", targs.group(1))] if targs else []
+        self.launches.append((kernel, (gx, gy, gz), threads, targs))
         self.on_launch(kernel, args)
         return 1 if self.fail(kernel) else 0
 

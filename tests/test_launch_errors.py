@@ -23,7 +23,7 @@ for name, call in calls.items():
     R.fail = lambda k: False
     out[name] = failed, time, call()
     L.lbm_set_state(h, R.plane(0), R.plane(1), R.plane(2), R.plane(3), 0)
-emit([out, sorted({k for k, _, _ in R.launches})])
+emit([out, sorted({k for k, *_ in R.launches})])
 """
 
 ROUTES = {

@@ -1,0 +1,36 @@
+"""Which kernels a step goes out as, by storage, sizes and statistics: both sides of every rule, on a
+host double of the HIP runtime (no GPU).  The rules are choices of speed between kernels of equal
+results; the figures behind them stand at their constants."""
+import pytest
+
+from host_double import double
+
+CODE = """
+R = Runtime()
+A, L = R.A, R.L
+shape, kw, planes, reference, steps = %r
+h = R.channel(*shape, **kw)
+if planes:
+    arr = (C.c_int32 * len(planes))(*planes)
+    assert L.lbm_stats(h, A.STATS_ATTACH, arr, len(planes), None, None) == A.LBM_OK
+if reference:
+    assert L.lbm_set_reference(h, R.plane(9)) == A.LBM_OK
+R.launches.clear()
+assert L.lbm_step(h, None, steps) == A.LBM_OK
+emit([l for l in R.launches if l[0].startswith("collide_")])
+"""
+
+
+def step(tmp_path, shape, planes=(), reference=False, steps=1, **kw):
+    return double(CODE % ((shape, kw, list(planes), reference, steps),), tmp_path)
+
+
+@pytest.mark.parametrize("shape,ranges", [((1536, 128, 384), 5), ((1536, 256, 384), 10), ((1040, 128, 128), 1)])
+def test_fp16_bulk_ranges_without_reference_offsets_only(shape, ranges, tmp_path):
+    names = [k for k, *_ in step(tmp_path, shape, storage=1)]
+    assert names == ["collide_bulk_kernel"] * ranges
+    whole = step(tmp_path, shape, storage=1, reference=True)
+    assert [k for k, *_ in whole] == ["collide_bulk_kernel"]
+    # every block of the lattice once, and at most what evens the eight XCDs' lists out
+    blocks = shape[0] * shape[1] // 4 * (shape[2] // 64)
+    assert blocks <= whole[0][1][0] <= blocks + 8 * 64 * ranges
