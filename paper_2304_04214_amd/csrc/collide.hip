@@ -439,9 +439,9 @@ constexpr int FUSED_SHORT_WAVES = 6;
 // costs a fixed ~10 us (its blocks run alone as a latency-bound wave), more
 // than the fused kernel's slower bulk path on small lattices, less on large.
 //
-// ZL: lanes of a row.  Lattices of at most 32 (16) spanwise nodes give a row 32
-// (16) lanes, so that a wave holds two (four) rows of the block's four and
-// fewer lanes are without a node.  us per step with 64 lanes -> with these:
+// ZL: lanes of a row (row_lanes).  Lattices of at most 32 (16) spanwise nodes
+// give a row 32 (16) lanes, so that a wave holds two (four) rows of the block's
+// four and fewer lanes are without a node.  us per step with 64 lanes -> with these:
 // 400x40x32 24.1 -> 20.6, 64x32x32 9.9 -> 7.6, 600x60x24 32.2 -> 28.7,
 // 200x20x16 13.4 -> 10.3, 880x80x16 56.0 -> 55.1 (bound by the padded bricks'
 // 128-byte lines).
@@ -752,9 +752,10 @@ void launch_bulk_kernel(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
     if (nt == 0) return;
     auto go = [&](auto FORCE, auto REF, auto NT) {
       constexpr bool F = FORCE.value, R = REF.value, N = NT.value;
-      if (h->cfg.nz <= 16)
+      const int lanes = row_lanes(h->cfg);
+      if (lanes == 16)
         collide_fused_kernel<true, F, R, N, 16><<<nt, YROWS * 16, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
-      else if (h->cfg.nz <= 32)
+      else if (lanes == 32)
         collide_fused_kernel<true, F, R, N, 32><<<nt, YROWS * 32, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
       else
         collide_fused_kernel<true, F, R, N, ZT><<<nt, BLOCK, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);

@@ -57,6 +57,18 @@ inline int64_t touched_bytes(const lbm_config& c) {
   const int64_t line = 128, el = c.storage == LBM_STORE_F32 ? 4 : 2;
   return 2 * (int64_t)Q * c.nx * c.ny * (c.nz / ZT * el * ZT + (el * (c.nz % ZT) + line - 1) / line * line);
 }
+// Lanes of a row in the fused FP16 kernel.  Short rows (collide_fused_kernel) on
+// lattices that the caches hold much of: beyond, the kernel is bound by memory,
+// and blocks of one or two waves lose.  us per three steps, 64 lanes -> short
+// rows, by the touched bytes: nz = 16 298 MB 139 -> 130, 340 MB 156 -> 164, 400
+// MB 181 -> 200, 500 MB 222 -> 305; nz = 24 298 MB 139 -> 128, 340 MB 157 -> 156,
+// 400 MB 181 -> 187, 500 MB 223 -> 287; nz = 32 340 MB 155 -> 137, 800 MB 347 ->
+// 360.
+constexpr int64_t SHORT_ROWS_MAX_BYTES[2] = {int64_t(288) << 20, int64_t(320) << 20};  // 16 lanes, 32 lanes
+inline int row_lanes(const lbm_config& c) {
+  if (c.nz > 32 || touched_bytes(c) > SHORT_ROWS_MAX_BYTES[c.nz > 16]) return ZT;
+  return c.nz > 16 ? 32 : 16;
+}
 // Static device scratch of stg_inlet_fill_noalloc (per device, for the process
 // lifetime): the STG tables of one call must fit.
 constexpr size_t NOALLOC_STG_BYTES = size_t(4) << 20;

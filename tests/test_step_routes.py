@@ -34,3 +34,18 @@ def test_fp16_bulk_ranges_without_reference_offsets_only(shape, ranges, tmp_path
     # every block of the lattice once, and at most what evens the eight XCDs' lists out
     blocks = shape[0] * shape[1] // 4 * (shape[2] // 64)
     assert blocks <= whole[0][1][0] <= blocks + 8 * 64 * ranges
+
+
+def lattice(nz, mb, storage, ny=90):
+    """The lattice of ny x nz whose nodes touch closest to mb million bytes of 128-byte lines."""
+    el = 4 if storage == 0 else 2
+    line = 2 * 19 * (-(-el * nz // 128) * 128) * ny
+    return round(mb * 1e6 / line), ny, nz
+
+
+@pytest.mark.parametrize("nz,mb,lanes", [(16, 60, 16), (16, 300, 16), (16, 305, 64), (9, 500, 64), (1, 290, 16),
+                                         (17, 300, 32), (32, 330, 32), (32, 340, 64), (24, 800, 64), (33, 60, 64)])
+def test_short_rows_within_the_caches_only(nz, mb, lanes, tmp_path):
+    for ref in (False, True):
+        (name, grid, threads, targs), = step(tmp_path, lattice(nz, mb, 1), reference=ref, storage=1)
+        assert name == "collide_fused_kernel" and threads == 4 * lanes and targs[-1] == lanes
