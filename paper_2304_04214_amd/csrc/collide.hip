@@ -692,7 +692,7 @@ void fill_args(lbm_ctx* h, CollideArgs& a, int src, int dst) {
   // much of the state the last one wrote in the Infinity Cache (the limits are at
   // their constants).
   const int64_t touched = touched_bytes(c);
-  a.nt_store = touched > NT_STORE_MIN_BYTES || (h->split && c.nz > 32 && touched < NT_STORE_BELOW_F16) ||
+  a.nt_store = touched > nt_store_min(c) || (h->split && c.nz > 32 && touched < NT_STORE_BELOW_F16) ||
                (h->last_step && touched > NT_LAST_MIN_BYTES[h->split]);
   a.has_g = (c.g[0] != 0.0 || c.g[1] != 0.0 || c.g[2] != 0.0) ? 1 : 0;
   a.tau0 = (float)c.tau0;

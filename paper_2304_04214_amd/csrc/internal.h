@@ -37,13 +37,30 @@ constexpr int CHUNK_BLOCKS = 30000;
 // 8014, 1536x192x384 5983 -> 6038, 1101x120x261 2207 -> 2230, 1536x128x384 4035 ->
 // 4069) and the step keeps one dispatch.
 constexpr int CHUNK_BLOCKS_F16 = 60000;
-// Where the 128-byte lines that the nodes of both state buffers touch are
-// together more than this: non-temporal population stores (the 256 MB Infinity
-// Cache holds too little of the state from one step to the next).  us per step,
-// non-temporal -> cached: FP32 400x64x64 (249 MB) 44.5 -> 38.9, 480x64x64
-// (299 MB) 52.6 -> 47.8, 520x64x64 (324 MB) 56.8 -> 59.2; FP16 800x64x64
+// Bytes of the 128-byte lines that the nodes of both state buffers touch.
+constexpr int64_t LINE = 128;
+inline int64_t row_bytes(const lbm_config& c) { return (c.storage == LBM_STORE_F32 ? 4 : 2) * (int64_t)c.nz; }
+inline int64_t touched_bytes(const lbm_config& c) {
+  return 2 * (int64_t)Q * c.nx * c.ny * ((row_bytes(c) + LINE - 1) / LINE * LINE);
+}
+// Where these are more than this: non-temporal population stores (the 256 MB
+// Infinity Cache holds too little of the state from one step to the next).  us
+// per step, non-temporal -> cached: FP32 400x64x64 (249 MB) 44.5 -> 38.9,
+// 480x64x64 (299 MB) 52.6 -> 47.8, 520x64x64 (324 MB) 56.8 -> 59.2; FP16 800x64x64
 // (249 MB) 47.5 -> 45.1, 400x40x32 20.0 -> 18.0, 600x80x10 36 -> 29.9.
+// Rows that end within a line turn earlier: FP32 at 285 to 300 MB, 183x80x112 46.9
+// -> 48.2, 193x80x100 49.2 -> 50.6 (at 270 MB still 44.7 -> 42.9); FP16 with 64-lane
+// rows that use at most half of their last line from 255 MB, 341x80x80 46.4 -> 48.1,
+// 353x80x70 47.8 -> 51.0, 170x80x200 49.0 -> 50.6 (at 245 MB 43.5 -> 41.9); with more
+// of it used they gain to the end (353x80x112 53.4 -> 52.1).
 constexpr int64_t NT_STORE_MIN_BYTES = int64_t(288) << 20;
+constexpr int64_t NT_STORE_MIN_PART[2] = {int64_t(268) << 20, int64_t(236) << 20};  // FP32, FP16
+inline int64_t nt_store_min(const lbm_config& c) {
+  const int64_t last = row_bytes(c) % LINE;
+  const bool f16 = c.storage != LBM_STORE_F32;
+  const bool part = f16 ? c.nz > 32 && last > 0 && last <= LINE / 2 : last > 0;
+  return part ? NT_STORE_MIN_PART[f16] : NT_STORE_MIN_BYTES;
+}
 // FP16 storage with 64-lane rows (nz > 32) also below this: the kernel is short
 // and the cached lines are written back at its end (64x64x64, periodic, 8.6 ->
 // 9.9 us with cached stores, 128x64x64 12.4 -> 12.6, 256x64x64 18.9 -> 18.7).
@@ -53,10 +70,6 @@ constexpr int64_t NT_STORE_BELOW_F16 = int64_t(56) << 20;
 // steps on states in turn, FP16 99x107x227 97 -> 89 us a call, 320x128x24 112 ->
 // 106, FP32 743x17x100 three steps 167 -> 160).
 constexpr int64_t NT_LAST_MIN_BYTES[2] = {int64_t(192) << 20, int64_t(64) << 20};
-inline int64_t touched_bytes(const lbm_config& c) {
-  const int64_t line = 128, el = c.storage == LBM_STORE_F32 ? 4 : 2;
-  return 2 * (int64_t)Q * c.nx * c.ny * (c.nz / ZT * el * ZT + (el * (c.nz % ZT) + line - 1) / line * line);
-}
 // Lanes of a row in the fused FP16 kernel.  Short rows (collide_fused_kernel) on
 // lattices that the caches hold much of: beyond, the kernel is bound by memory,
 // and blocks of one or two waves lose.  us per three steps, 64 lanes -> short

@@ -49,3 +49,18 @@ def test_short_rows_within_the_caches_only(nz, mb, lanes, tmp_path):
     for ref in (False, True):
         (name, grid, threads, targs), = step(tmp_path, lattice(nz, mb, 1), reference=ref, storage=1)
         assert name == "collide_fused_kernel" and threads == 4 * lanes and targs[-1] == lanes
+
+
+@pytest.mark.parametrize("storage,nz,mb,nt", [
+    # FP32: 288 MiB (302 MB) with whole lines, 268 MiB (281 MB) with a part of one
+    (0, 64, 300, 0), (0, 64, 305, 1), (0, 96, 300, 0), (0, 112, 278, 0), (0, 112, 284, 1), (0, 100, 284, 1),
+    (0, 33, 284, 1), (0, 33, 270, 0),
+    # FP16 with 64-lane rows: 236 MiB (247 MB) where at most half of the last line is used
+    (1, 64, 300, 0), (1, 64, 305, 1), (1, 100, 300, 0), (1, 48, 300, 0), (1, 96, 250, 1), (1, 80, 250, 1),
+    (1, 70, 245, 0), (1, 200, 250, 1), (1, 200, 244, 0), (1, 97, 300, 0)])
+def test_cached_stores_within_the_infinity_cache_only(storage, nz, mb, nt, tmp_path):
+    """The first of two steps (a call's last one stores non-temporally on large lattices)."""
+    first, last = step(tmp_path, lattice(nz, mb, storage, ny=80), steps=2, storage=storage)
+    assert first[0] == ("collide_fused_kernel" if storage else "collide_general_kernel")
+    template = 3 if storage else 1
+    assert first[3][template] == nt and last[3][template] == 1
