@@ -791,7 +791,7 @@ void launch_bulk_kernel(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
 // chunks update disjoint nodes from s_n, so their order is free).
 void launch_edge_kernels(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
   const bool f16 = h->cfg.storage == LBM_STORE_F16DEV;
-  if (h->rows) {
+  if (h->rows && !(a.stats_on && h->rows_lose_sampled)) {
     launch_rows(h, a, stream);  // all blocks
     return;
   }

@@ -182,8 +182,10 @@ struct lbm_ctx {
   bool split = false;
   bool fused = false;
   // Lattices of few spanwise nodes: rows per block of the row kernel (rows.hip;
-  // 0: not used), its threads and its blocks per plane.
+  // 0: not used), its threads and its blocks per plane, and whether steps whose
+  // statistics are sampled go to the general kernel all the same.
   int rows = 0, row_threads = 0, row_groups = 0;
+  bool rows_lose_sampled = false;
   double* d_stats = nullptr;
   size_t stats_bytes = 0;
   double* d_wall_acc = nullptr;  // [2][nx][zc], with the wall model

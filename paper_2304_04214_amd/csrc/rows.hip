@@ -246,6 +246,15 @@ __global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int x
 // of which a quarter idles); above, the largest of up to 256 threads (400x40x32
 // 15.3 us, 16.9 with 128).  Every block has at least two rows, a wall row and the
 // row next to it.
+// A wave sums a sampled plane's rows a few at a time (four of up to 16 lanes, two
+// of 32, at twice the adds), the general kernel one each: where a block's rows
+// take many turns and the launch is short enough to wait for them, sampled steps
+// go to the general kernel.  us per two steps with four planes, general -> this
+// one, by turns (twice as many with 32 lanes) and blocks of the general kernel:
+// 8 turns 41x60x2 (615) 22.7 -> 29.0, 206x60x2 (3090) 36.2 -> 40.0, 308x60x2 (4620)
+// 44.7 -> 42.4; 3 turns 41x20x4 (205) 19.7 -> 20.2; 4 turns 41x60x4 (615) 22.5 ->
+// 22.2, 41x60x24 (615) 21.7 -> 22.1, 103x60x24 (1545) 30.1 -> 27.4; 2 turns 41x20x12
+// (205) 19.5 -> 18.8.
 void plan_rows(lbm_ctx* h) {
   const lbm_config& c = h->cfg;
   h->rows = 0;
@@ -262,6 +271,10 @@ void plan_rows(lbm_ctx* h) {
     h->row_threads = threads;
     h->row_groups = groups;
   }
+  if (!h->rows) return;
+  const int per = c.nz <= 16 ? 4 : 2, at_once = h->row_threads / ZT * per;
+  const int turns = (h->rows + at_once - 1) / at_once * (4 / per);
+  h->rows_lose_sampled = (int64_t)c.nx * h->yg < 600 * (int64_t)(turns - 2);
 }
 
 // One dispatch per x-range, as the general kernel.  The caller reads the launch error:
