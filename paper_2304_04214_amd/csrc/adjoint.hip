@@ -39,8 +39,10 @@
 namespace lbm {
 namespace {
 
-// of both lambda buffers, see launch_adjoint
-constexpr int64_t NT_PULL_MIN_BYTES = int64_t(118) << 20, NT_PULL_MAX_BYTES = int64_t(320) << 20;
+// of both lambda buffers, see launch_adjoint: FP32 states with rows of whole
+// 128-byte lines of lambda, FP32 states with others, FP16 states; all up to the last
+constexpr int64_t NT_PULL_MIN_BYTES[3] = {int64_t(118) << 20, int64_t(190) << 20, int64_t(225) << 20};
+constexpr int64_t NT_PULL_MAX_BYTES = int64_t(320) << 20;
 
 // Moments (M v)_k of a population vector in the Appendix A.1 basis, from its
 // opposite-pair sums and differences.
@@ -753,16 +755,21 @@ hipError_t launch_adjoint(lbm_ctx* h, const AdjointArgs& args, int storage_f16, 
   // A step reads its state once and no step soon again; the lambda it writes is
   // the next one's input.  Where the two lambda buffers are much of the Infinity
   // Cache the state is loaded non-temporally, so that it does not push them out:
-  // us per step 400x64x64 72.3 -> 63.2, 256x64x64 44.8 -> 43.1, 200x64x64 (125 MB
-  // of lambda) 37.9 -> 36.0, with FP16 states 35.4 -> 35.1, but 180x64x64 with FP16
-  // states (112 MB) 32.0 -> 32.8, 128x64x64 25.4 -> 26.2.  Lambda buffers larger than the
-  // cache are not kept in any case (189x127x116, 468 MB, 159 -> 169); with more
-  // than two bricks a row the lines that neighbouring bricks share are read again
-  // (80x68x279 66 -> 68).
+  // us per four steps 400x64x64 289 -> 254, 320x64x64 223 -> 210, 256x64x64 180 -> 173,
+  // 200x64x64 (125 MB of lambda) 152 -> 144, 520x64x64 (324 MB) 364 -> 345; with FP16
+  // states 440x64x64 (274 MB) 288 -> 271, 480x64x64 306 -> 297.  A sweep gains that;
+  // one or two steps on a state that the cache still holds, or on others in turn, gain
+  // less or lose a little where lambda is small and what is gained is too: FP16 states
+  // up to 235 MB of lambda one step 256x64x64 40.1 -> 41.6, 320x64x64 47.7 -> 49.7, two
+  // of 110x90x101 in turn 110 -> 114 (20 steps of a gradient run 1.00x to 1.02x); FP32
+  // states with rows that end within a line up to 200 MB, two steps in turn 94x90x101
+  // 109 -> 117.  Lambda buffers larger than the cache are not kept in any case
+  // (189x127x116, 468 MB, 159 -> 169 a step); with more than two bricks a row the lines
+  // that neighbouring bricks share are read again (80x68x279 66 -> 68).
   lbm_config lam = h->cfg;
   lam.storage = LBM_STORE_F32;
-  const bool nt = touched_bytes(lam) > NT_PULL_MIN_BYTES && touched_bytes(lam) < NT_PULL_MAX_BYTES &&
-                  lam.nz <= 2 * ZT;
+  const int64_t least = NT_PULL_MIN_BYTES[storage_f16 ? 2 : row_bytes(lam) % LINE != 0];
+  const bool nt = touched_bytes(lam) > least && touched_bytes(lam) < NT_PULL_MAX_BYTES && lam.nz <= 2 * ZT;
   auto go = [&](auto F16, auto REF, const float* dref, const float* dpull) {
     constexpr bool F = F16.value, R = REF.value;
     if (nt)

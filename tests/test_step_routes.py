@@ -73,3 +73,28 @@ def test_cached_stores_within_the_infinity_cache_only(storage, nz, mb, nt, tmp_p
 def test_sampled_steps_leave_the_row_kernel_where_its_sums_take_longer(shape, sampled, tmp_path):
     assert [k for k, *_ in step(tmp_path, shape)] == ["collide_rows_kernel"]
     assert [k for k, *_ in step(tmp_path, shape, planes=[1, 3])] == ["collide_%s_kernel" % sampled]
+
+
+ADJOINT = """
+R = Runtime()
+A, L = R.A, R.L
+shape, storage, reference = %r
+h = R.channel(*shape, storage=storage)
+if reference:
+    assert L.lbm_set_reference(h, R.plane(9)) == A.LBM_OK
+R.launches.clear()
+p = R.plane
+assert L.lbm_adjoint_step(h, None, p(10), None, 1.0, p(11), None, p(12), *[None] * 6) == A.LBM_OK
+emit([l for l in R.launches if l[0] == "adjoint_kernel"])
+"""
+
+
+@pytest.mark.parametrize("storage,nz,mb,nt", [
+    (0, 64, 120, 0), (0, 64, 128, 1), (0, 64, 330, 1), (0, 64, 340, 0), (0, 128, 128, 1), (0, 160, 200, 0),
+    (0, 101, 194, 0), (0, 101, 205, 1), (0, 40, 205, 1), (0, 70, 130, 0),
+    (1, 64, 230, 0), (1, 64, 240, 1), (1, 101, 230, 0), (1, 101, 240, 1), (1, 64, 340, 0)])
+def test_adjoint_pulls_the_state_non_temporally_where_sweeps_gain(storage, nz, mb, nt, tmp_path):
+    shape = lattice(nz, mb, 0)  # lambda is FP32
+    for ref in (False, True)[:1 + storage]:
+        (_, _, _, targs), = double(ADJOINT % ((shape, storage, ref),), tmp_path)
+        assert targs == [storage, int(ref), nt]
