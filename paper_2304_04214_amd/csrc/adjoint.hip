@@ -223,7 +223,7 @@ __device__ __forceinline__ void node_adjoint(const AdjointArgs& A, AdjLds& L, in
     for (int k = 0; k < 5; ++k) {
       const int i = OUT5[k];
       const float up = pull_dir<F16>(a, g2, i, col, 0.f);
-      f[i] = a.out_wh * a.hist_in[(k * a.ny + y) * a.nz + z] + a.out_wu * up;
+      f[i] = outlet_value(a, a.hist_in[(k * a.ny + y) * a.nz + z], up);
     }
   }
   float rin = 0.f;

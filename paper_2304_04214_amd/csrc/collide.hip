@@ -69,7 +69,7 @@ __device__ __forceinline__ void x_rules(const CollideArgs& a, int x, int y, int 
       const int i = OUT5[k];
       const float up = pull_dir<F16>(a, g2, i, col, 0.f);
       const int hidx = (k * a.ny + y) * a.nz + z;
-      const float v = a.out_wh * a.hist_in[hidx] + a.out_wu * up;
+      const float v = outlet_value(a, a.hist_in[hidx], up);
       f[i] = v;
       if (store) a.hist_out[hidx] = v;
     }

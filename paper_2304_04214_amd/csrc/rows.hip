@@ -137,7 +137,7 @@ __global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int x
   if (outlet) {
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-      const float v = __builtin_fmaf(a.out_wh, e0[k], a.out_wu * e1[k]);
+      const float v = outlet_value(a, e0[k], e1[k]);
       f[OUT5[k]] = v;
       if (mine) a.hist_out[k * a.ny * a.nz + pz] = v;
     }

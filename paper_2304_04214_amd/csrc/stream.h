@@ -389,6 +389,13 @@ __device__ __forceinline__ float newton_utau(const CollideArgs& a, float ua) {
   return ut;
 }
 
+// Outlet rule of a population with c_x < 0, from its value at the last step and
+// the upstream one of this step.  The fused multiply-add is written out: the
+// kernels that share the rule give equal bits.
+__device__ __forceinline__ float outlet_value(const CollideArgs& a, float last, float up) {
+  return __builtin_fmaf(a.out_wh, last, a.out_wu * up);
+}
+
 // Regularised inlet populations (Sec. III.A, Eq. (26)-(31)): Zou-He density
 // from the known c_x <= 0 populations, second-order equilibrium at u_in, and
 // the non-equilibrium part rebuilt from Pi_neq with the unknown c_x > 0
