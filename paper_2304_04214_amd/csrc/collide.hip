@@ -227,12 +227,12 @@ struct RowRef {
   }
 };
 
-// A block whose 3 x 3 source rows all lie inside the lattice (see the
-// block lists): plain shifted pulls, no boundary rule.
+// FP16 storage: a block whose 3 x 3 source rows all lie inside the lattice (see
+// the block lists): plain shifted pulls, no boundary rule.
 // dref / dpull: the reference offsets (REF), passed as restrict kernel
 // arguments so that their loads need not be ordered after the stores.
 // ZL < 64: lref takes the offsets (RowRef).
-template <bool F16, bool FORCE, bool REF, bool NT = true, int ZL = ZT>
+template <bool FORCE, bool REF, bool NT = true, int ZL = ZT>
 __device__ __forceinline__ void plain_block(const CollideArgs& a, int x, int zci, int gy,
                                             const float* __restrict__ dref, const float* __restrict__ dpull,
                                             float* lref = nullptr) {
@@ -243,52 +243,46 @@ __device__ __forceinline__ void plain_block(const CollideArgs& a, int x, int zci
   const int zraw = zci * ZT + lane;
   const bool active = zraw < a.nz;
   const int z = active ? zraw : a.nz - 1;
-  const Col col = make_col<F16>(a, z);
+  const Col col = make_col<true>(a, z);
   const Geo g = make_geo(a, x, y);
   RowRef<ZL> rr;
   if (REF && ZL < ZT) rr.load(a, dref, base);
-  typename Pop<F16>::Raw r[Q];
+  Pop<true>::Raw r[Q];
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
     const uint32_t cs = CZ[i] == 1 ? col.bm : (CZ[i] == -1 ? col.bp : col.b0);
-    r[i] = Pop<F16>::raw(row_ptr<F16>(a.src, rowpart(a, g.xs[CX[i] + 1], g.ys[CY[i] + 1]) + (uint32_t)i * ZT), cs);
+    r[i] = Pop<true>::raw(row_ptr<true>(a.src, rowpart(a, g.xs[CX[i] + 1], g.ys[CY[i] + 1]) + (uint32_t)i * ZT), cs);
   }
   if (REF && ZL < ZT) rr.store(lref);
-  // FP16 storage computes on the deviations h = f - w directly (no w added on
-  // load or subtracted on store); FP32 storage on the populations.
+  // on the deviations h = f - w directly (no w added on load or subtracted on store)
   float f[Q];
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
-    if (!F16)
-      f[i] = Pop<F16>::cvt(i, r[i], 0.f);
-    else if (REF)
+    if (REF)
       f[i] = Pop<true>::cvt_dev(r[i], ZL < ZT ? lref[(w + 1 - CY[i]) * Q + i] : dpull[y * Q + i]);  // uniform row: scalar loads
     else
       f[i] = Pop<true>::cvt_dev(r[i]);
   }
   const Pairs pr = make_pairs(f);
-  const float rhoh = pr.A + pr.Bx + f[9];  // sum of h (F16) or rho (F32)
-  const float rho = F16 ? 1.f + rhoh : rhoh;
+  const float rhoh = pr.A + pr.Bx + f[9], rho = 1.f + rhoh;
   const float jx = (pr.d[3] + pr.d[7]) - (pr.d[1] + pr.d[5] + pr.d[8]);
   const float jy = pr.d[4] - (pr.d[0] + pr.d[5] + pr.d[6] + pr.d[7]);
   const float jz = -(pr.d[0] + pr.d[1] + pr.d[2] + pr.d[3] + pr.d[4]);
   float ux, uy, uz;
   const Tau0 t0 = tau0_of_x(a, x);
   if (FORCE)
-    collide<true, F16>(a, t0, f, pr, rho, jx, jy, jz, rho * a.g[0], rho * a.g[1], rho * a.g[2], ux, uy, uz, rhoh);
+    collide<true, true>(a, t0, f, pr, rho, jx, jy, jz, rho * a.g[0], rho * a.g[1], rho * a.g[2], ux, uy, uz, rhoh);
   else
-    collide<false, F16>(a, t0, f, pr, rho, jx, jy, jz, 0.f, 0.f, 0.f, ux, uy, uz, rhoh);
+    collide<false, true>(a, t0, f, pr, rho, jx, jy, jz, 0.f, 0.f, 0.f, ux, uy, uz, rhoh);
   if (!(rho > 0.f && rho < 1e30f)) atomicOr(a.err, ERRBIT_NONFINITE);
   if (active && owned) {
-    char* p = const_cast<char*>(row_ptr<F16>(a.dst, rowpart(a, x, y)));
+    char* p = const_cast<char*>(row_ptr<true>(a.dst, rowpart(a, x, y)));
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-      if (F16 && REF)
-        Pop<true>::stp_dev<NT>(p + i * ZT * Pop<F16>::ES, col.b0, f[i], ZL < ZT ? lref[(w + 1) * Q + i] : dref[y * Q + i]);
-      else if (F16)
-        Pop<true>::stp_dev<NT>(p + i * ZT * Pop<F16>::ES, col.b0, f[i]);
+      if (REF)
+        Pop<true>::stp_dev<NT>(p + i * ZT * Pop<true>::ES, col.b0, f[i], ZL < ZT ? lref[(w + 1) * Q + i] : dref[y * Q + i]);
       else
-        Pop<F16>::template stp<NT>(p + i * ZT * Pop<F16>::ES, i, col.b0, f[i], 0.f);
+        Pop<true>::stp_dev<NT>(p + i * ZT * Pop<true>::ES, col.b0, f[i]);
     }
   }
 }
@@ -298,7 +292,7 @@ __device__ __forceinline__ void plain_block(const CollideArgs& a, int x, int zci
 // the wall model (the wall row's neighbour velocity through LDS).  Density
 // and momentum are summed directly so that the pair sums of the collision
 // are not live across the Newton solve (fewer registers).
-template <bool F16, bool REF, bool NT = true, int ZL = ZT>
+template <bool REF, bool NT = true, int ZL = ZT>
 __device__ __forceinline__ void wall_block(const CollideArgs& a, int x, int zci, int gy, float (*lds_u2)[2][ZL],
                                            const float* __restrict__ dref, float* lref = nullptr) {
   const int lane = threadIdx.x & (ZL - 1);
@@ -308,19 +302,17 @@ __device__ __forceinline__ void wall_block(const CollideArgs& a, int x, int zci,
   const int zraw = zci * ZT + lane;
   const bool active = zraw < a.nz;
   const int z = active ? zraw : a.nz - 1;
-  const Col col = make_col<F16>(a, z);
+  const Col col = make_col<true>(a, z);
   const Geo g = make_geo(a, x, y);
   RowRef<ZL> rr;
   if (REF && ZL < ZT) rr.load(a, dref, base);
-  typename Pop<F16>::Raw r[Q];
-  issue_pulls<F16, ZL == ZT>(a, g, col, r);  // every x source exists; the y walls redirect
+  Pop<true>::Raw r[Q];
+  issue_pulls<true, ZL == ZT>(a, g, col, r);  // every x source exists; the y walls redirect
   if (REF && ZL < ZT) rr.store(lref);
   float f[Q];
 #pragma unroll
   for (int i = 0; i < Q; ++i) {
-    if (!F16) {
-      f[i] = Pop<F16>::cvt(i, r[i], 0.f);
-    } else if (REF && ZL < ZT) {
+    if (REF && ZL < ZT) {
       int plane, ysrc;
       pull_plane_row(a, g, i, plane, ysrc);
       f[i] = Pop<true>::cvt_dev(r[i], lref[(CY[i] != 0 && g.yout[CY[i] + 1] ? w + 1 : w + 1 - CY[i]) * Q + plane]);
@@ -339,7 +331,7 @@ __device__ __forceinline__ void wall_block(const CollideArgs& a, int x, int zci,
     if (CY[i]) jy += CY[i] * f[i];
     if (CZ[i]) jz += CZ[i] * f[i];
   }
-  const float rho = F16 ? 1.f + rhoh : rhoh;
+  const float rho = 1.f + rhoh;
   float Fx = rho * a.g[0], Fy = rho * a.g[1], Fz = rho * a.g[2];
   if (a.wall_model) {
     const bool bot = base == 0, top = base == a.ny - YROWS;
@@ -370,25 +362,23 @@ __device__ __forceinline__ void wall_block(const CollideArgs& a, int x, int zci,
   }
   float ux, uy, uz;
   const Pairs pr = make_pairs(f);
-  collide<true, F16>(a, tau0_of_x(a, x), f, pr, rho, jx, jy, jz, Fx, Fy, Fz, ux, uy, uz, rhoh);
+  collide<true, true>(a, tau0_of_x(a, x), f, pr, rho, jx, jy, jz, Fx, Fy, Fz, ux, uy, uz, rhoh);
   if (!(rho > 0.f && rho < 1e30f)) atomicOr(a.err, ERRBIT_NONFINITE);
   if (active && owned) {
-    char* p = const_cast<char*>(row_ptr<F16>(a.dst, rowpart(a, x, y)));
+    char* p = const_cast<char*>(row_ptr<true>(a.dst, rowpart(a, x, y)));
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-      if (F16 && REF)
-        Pop<true>::stp_dev<NT>(p + i * ZT * Pop<F16>::ES, col.b0, f[i], ZL < ZT ? lref[(w + 1) * Q + i] : dref[y * Q + i]);
-      else if (F16)
-        Pop<true>::stp_dev<NT>(p + i * ZT * Pop<F16>::ES, col.b0, f[i]);
+      if (REF)
+        Pop<true>::stp_dev<NT>(p + i * ZT * Pop<true>::ES, col.b0, f[i], ZL < ZT ? lref[(w + 1) * Q + i] : dref[y * Q + i]);
       else
-        Pop<F16>::template stp<NT>(p + i * ZT * Pop<F16>::ES, i, col.b0, f[i], 0.f);
+        Pop<true>::stp_dev<NT>(p + i * ZT * Pop<true>::ES, col.b0, f[i]);
     }
   }
 }
 
 // Interior and wall blocks (block-uniform choice): the lean kernel, so it
 // keeps few registers and many waves in flight to hide HBM latency.
-template <bool F16, bool FORCE, bool REF>
+template <bool FORCE, bool REF>
 __global__ __launch_bounds__(BLOCK) void collide_bulk_kernel(CollideArgs a, const int* __restrict__ blist,
                                                              const float* __restrict__ dref,
                                                              const float* __restrict__ dpull) {
@@ -399,9 +389,9 @@ __global__ __launch_bounds__(BLOCK) void collide_bulk_kernel(CollideArgs a, cons
   block_coords(a, e, x, zci, gy);
   const int base = min(YROWS * gy, a.ny - YROWS);
   if (a.ywall != LBM_Y_PERIODIC && (base == 0 || base == a.ny - YROWS))
-    wall_block<F16, REF>(a, x, zci, gy, lds_u2, dref);
+    wall_block<REF>(a, x, zci, gy, lds_u2, dref);
   else
-    plain_block<F16, FORCE, REF>(a, x, zci, gy, dref, dpull);
+    plain_block<FORCE, REF>(a, x, zci, gy, dref, dpull);
 }
 
 template <bool F16, bool NT = true>
@@ -445,7 +435,7 @@ constexpr int FUSED_SHORT_WAVES = 6;
 // 400x40x32 24.1 -> 20.6, 64x32x32 9.9 -> 7.6, 600x60x24 32.2 -> 28.7,
 // 200x20x16 13.4 -> 10.3, 880x80x16 56.0 -> 55.1 (bound by the padded bricks'
 // 128-byte lines).
-template <bool F16, bool FORCE, bool REF, bool NT, int ZL>
+template <bool FORCE, bool REF, bool NT, int ZL>
 __global__ __launch_bounds__(YROWS* ZL) __attribute__((amdgpu_waves_per_eu(ZL == ZT ? 8 : FUSED_SHORT_WAVES)))
 void collide_fused_kernel(CollideArgs a, const int* __restrict__ gl, int n_gen, const int* __restrict__ bl,
                           const float* __restrict__ dref, const float* __restrict__ dpull) {
@@ -463,13 +453,13 @@ void collide_fused_kernel(CollideArgs a, const int* __restrict__ gl, int n_gen, 
     const int zraw = zci * ZT + lane;
     const bool active = zraw < a.nz;
     const int z = active ? zraw : a.nz - 1;
-    const Col col = make_col<F16>(a, z);
+    const Col col = make_col<true>(a, z);
     const Geo g = make_geo(a, x, y);
-    typename Pop<F16>::Raw r[Q];
-    issue_pulls<F16, ZL == ZT>(a, g, col, r);
+    Pop<true>::Raw r[Q];
+    issue_pulls<true, ZL == ZT>(a, g, col, r);
     float f[Q];
-    convert_pulls<F16, ZL == ZT>(a, g, r, f);
-    node_update<F16, NT, ZL>(a, x, y, z, lane, base, zci, owned, active, col, f, lds_u2);
+    convert_pulls<true, ZL == ZT>(a, g, r, f);
+    node_update<true, NT, ZL>(a, x, y, z, lane, base, zci, owned, active, col, f, lds_u2);
     return;
   }
   const int e = bl[b - n_gen];
@@ -479,9 +469,9 @@ void collide_fused_kernel(CollideArgs a, const int* __restrict__ gl, int n_gen, 
   const int base = min(YROWS * gy, a.ny - YROWS);
   __shared__ float lref[REF && ZL < ZT ? RowRef<ZL>::N : 1];
   if (a.ywall != LBM_Y_PERIODIC && (base == 0 || base == a.ny - YROWS))
-    wall_block<F16, REF, NT, ZL>(a, x, zci, gy, lds_u2, dref, lref);
+    wall_block<REF, NT, ZL>(a, x, zci, gy, lds_u2, dref, lref);
   else
-    plain_block<F16, FORCE, REF, NT, ZL>(a, x, zci, gy, dref, dpull, lref);
+    plain_block<FORCE, REF, NT, ZL>(a, x, zci, gy, dref, dpull, lref);
 }
 
 // Pre-force velocity (u_x, u_z) of node (x, y, z) after streaming and the
@@ -754,11 +744,11 @@ void launch_bulk_kernel(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
       constexpr bool F = FORCE.value, R = REF.value, N = NT.value;
       const int lanes = row_lanes(h->cfg);
       if (lanes == 16)
-        collide_fused_kernel<true, F, R, N, 16><<<nt, YROWS * 16, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
+        collide_fused_kernel<F, R, N, 16><<<nt, YROWS * 16, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
       else if (lanes == 32)
-        collide_fused_kernel<true, F, R, N, 32><<<nt, YROWS * 32, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
+        collide_fused_kernel<F, R, N, 32><<<nt, YROWS * 32, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
       else
-        collide_fused_kernel<true, F, R, N, ZT><<<nt, BLOCK, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
+        collide_fused_kernel<F, R, N, ZT><<<nt, BLOCK, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
     };
     auto store = [&](auto FORCE, auto REF) {
       a.nt_store ? go(FORCE, REF, std::true_type{}) : go(FORCE, REF, std::false_type{});
@@ -772,18 +762,18 @@ void launch_bulk_kernel(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
   // x-chunk of it (see CHUNK_BLOCKS_F16).
   if (a.dref) {
     if (a.has_g)
-      collide_bulk_kernel<true, true, true><<<n, BLOCK, 0, stream>>>(a, bl, a.dref, a.dpull);
+      collide_bulk_kernel<true, true><<<n, BLOCK, 0, stream>>>(a, bl, a.dref, a.dpull);
     else
-      collide_bulk_kernel<true, false, true><<<n, BLOCK, 0, stream>>>(a, bl, a.dref, a.dpull);
+      collide_bulk_kernel<false, true><<<n, BLOCK, 0, stream>>>(a, bl, a.dref, a.dpull);
     return;
   }
   for (size_t k = 0; k + 1 < h->int_off.size(); ++k) {
     const int m = h->int_off[k + 1] - h->int_off[k];
     const int* bk = bl + h->int_off[k];
     if (a.has_g)
-      collide_bulk_kernel<true, true, false><<<m, BLOCK, 0, stream>>>(a, bk, nullptr, nullptr);
+      collide_bulk_kernel<true, false><<<m, BLOCK, 0, stream>>>(a, bk, nullptr, nullptr);
     else
-      collide_bulk_kernel<true, false, false><<<m, BLOCK, 0, stream>>>(a, bk, nullptr, nullptr);
+      collide_bulk_kernel<false, false><<<m, BLOCK, 0, stream>>>(a, bk, nullptr, nullptr);
   }
 }
 

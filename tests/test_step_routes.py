@@ -62,7 +62,7 @@ def test_cached_stores_within_the_infinity_cache_only(storage, nz, mb, nt, tmp_p
     """The first of two steps (a call's last one stores non-temporally on large lattices)."""
     first, last = step(tmp_path, lattice(nz, mb, storage, ny=80), steps=2, storage=storage)
     assert first[0] == ("collide_fused_kernel" if storage else "collide_general_kernel")
-    template = 3 if storage else 1
+    template = 2 if storage else 1
     assert first[3][template] == nt and last[3][template] == 1
 
 
