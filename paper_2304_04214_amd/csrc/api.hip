@@ -462,7 +462,11 @@ lbm_status lbm_stats(lbm_handle h, int32_t op, const int32_t* x_planes, int32_t 
       }
       const size_t bytes = sizeof(double) * (size_t)n_planes * ny * h->zc * 9;
       if (h->d_stats && h->stats_bytes == bytes && map == h->plane_of_x) {
-        // the planes attached before: buffers and block lists are theirs
+        // the planes attached before: buffers and block lists are theirs (refused under
+        // capture, as the synchronisation below refuses it)
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        HIPCHK(hipStreamIsCapturing(h->stream, &cap));
+        if (cap != hipStreamCaptureStatusNone) return LBM_ERR_HIP;
         HIPCHK(hipMemsetAsync(h->d_stats, 0, bytes, h->stream));
         if (h->d_wall_acc) HIPCHK(hipMemsetAsync(h->d_wall_acc, 0, sizeof(double) * 2 * nx * h->zc, h->stream));
         h->n_samples = 0;
