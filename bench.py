@@ -103,7 +103,7 @@ def time_channel(name, storage, steps, warmup, device, sponge=False, repeats=REP
     import torch
     ch, (nx, ny, nz) = make_channel(name, storage, device, sponge=sponge, shard=shard)
     N = nx * ny * nz
-    n_disp, disp_planes = ch.collide_dispatches()
+    n_disp, disp_planes = ch.timed_dispatches()
     ch.step(warmup)
     ch.sync()
     if not shard:
@@ -134,7 +134,7 @@ def time_channel(name, storage, steps, warmup, device, sponge=False, repeats=REP
                step_frac=bpn * N / (w["median"] * 1e-3) / 1e9 / HBM_PEAK_GBS,
                kernel_ms=k["median"], kernel_ms_min=k["min"], kernel_ms_max=k["max"], kernel_nodes=k_nodes,
                kernel_gbs=bpn * k_nodes / (k["median"] * 1e-3) / 1e9, status=status,
-               dispatches_per_step=n_disp if storage == "f32" else 1, planes_per_dispatch=disp_planes)
+               dispatches_per_step=n_disp, planes_per_dispatch=disp_planes)
     res["kernel_frac"] = res["kernel_gbs"] / HBM_PEAK_GBS
     ch.close()
     del ch

@@ -422,6 +422,12 @@ lbm_status lbm_kernel_timing(lbm_handle h, int32_t enable, double* total_ms, int
    may be NULL. */
 lbm_status lbm_collide_dispatches(lbm_handle h, int32_t* dispatches, int32_t* planes);
 
+/* The same of what lbm_kernel_timing counts as one launch: with LBM_STORE_F32
+   as lbm_collide_dispatches; with LBM_STORE_F16DEV the bulk kernel's dispatches
+   and the x-planes of each (the last may hold fewer), one of nx planes with a
+   storage reference (lbm_set_reference) or up to 2^24 nodes. */
+lbm_status lbm_timed_dispatches(lbm_handle h, int32_t* dispatches, int32_t* planes);
+
 /* Plain device copy kernel (bandwidth calibration): dst[0:bytes) = src[0:bytes),
    bytes a multiple of 16, both 16-byte aligned. */
 lbm_status lbm_copy_probe(const void* src, void* dst, int64_t bytes, void* hip_stream);

@@ -20,7 +20,7 @@ EXPORTED = [
     "lbm_init_equilibrium_f64",
     "lbm_inflow_reichardt", "stg_inlet_fill", "stg_inlet_fill_noalloc", "lbm_step", "lbm_stream_only", "lbm_export_f32", "lbm_import_f32",
     "lbm_set_reference", "lbm_state_elems",
-    "lbm_stats", "lbm_sync", "lbm_status_str", "lbm_kernel_timing", "lbm_collide_dispatches", "lbm_copy_probe", "lbm_lattice_tables",
+    "lbm_stats", "lbm_sync", "lbm_status_str", "lbm_kernel_timing", "lbm_collide_dispatches", "lbm_timed_dispatches", "lbm_copy_probe", "lbm_lattice_tables",
     "lbm_set_cs_smag", "lbm_adjoint_step", "lbm_step_record", "lbm_step_keep", "lbm_field_export", "lbm_field_import",
 ]
 
@@ -80,6 +80,7 @@ def lib():
             "lbm_sync": [P],
             "lbm_kernel_timing": [P, I32, P, P, P],
             "lbm_collide_dispatches": [P, P, P],
+            "lbm_timed_dispatches": [P, P, P],
             "lbm_copy_probe": [P, P, I64, P],
             "lbm_set_cs_smag": [P, D],
             "lbm_adjoint_step": [P, P, P, P, D, P, P, P, P, P, P, P, P, P],

@@ -336,6 +336,13 @@ class Channel:
         A.check(A.lib().lbm_collide_dispatches(self._h, C.byref(d), C.byref(p)), "lbm_collide_dispatches")
         return d.value, p.value
 
+    def timed_dispatches(self):
+        """The same of what kernel_timing counts as one launch (FP16: the bulk or the fused kernel)."""
+        d = C.c_int32()
+        p = C.c_int32()
+        A.check(A.lib().lbm_timed_dispatches(self._h, C.byref(d), C.byref(p)), "lbm_timed_dispatches")
+        return d.value, p.value
+
 
 def copy_probe(src, dst):
     """Plain device copy kernel of the library (bandwidth calibration)."""

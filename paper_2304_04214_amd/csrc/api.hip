@@ -741,6 +741,15 @@ lbm_status lbm_collide_dispatches(lbm_handle h, int32_t* dispatches, int32_t* pl
   return LBM_OK;
 }
 
+lbm_status lbm_timed_dispatches(lbm_handle h, int32_t* dispatches, int32_t* planes) {
+  if (!h) return LBM_ERR_ARG;
+  if (!h->split) return lbm_collide_dispatches(h, dispatches, planes);
+  const bool whole = h->fused || h->d_dref;  // see launch_bulk_kernel
+  if (dispatches) *dispatches = whole ? 1 : (int32_t)h->int_off.size() - 1;
+  if (planes) *planes = whole ? h->cfg.nx : h->int_planes;
+  return LBM_OK;
+}
+
 lbm_status lbm_copy_probe(const void* src, void* dst, int64_t bytes, void* hip_stream) {
   if (!src || !dst || bytes <= 0 || (bytes & 15) != 0) return LBM_ERR_ARG;
   if ((reinterpret_cast<uintptr_t>(src) & 15u) || (reinterpret_cast<uintptr_t>(dst) & 15u)) return LBM_ERR_SHAPE;

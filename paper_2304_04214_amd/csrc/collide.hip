@@ -953,7 +953,8 @@ hipError_t build_block_lists(lbm_ctx* h, const std::vector<int>& plane_of_x) {
   };
   const int planes = split ? c.nx : chunk_planes(CHUNK_BLOCKS);
   chunk(bd, planes, nullptr, h->bnd_off);
-  chunk(in, h->fused ? c.nx : chunk_planes(CHUNK_BLOCKS_F16), &in_heavy, h->int_off);
+  h->int_planes = h->fused ? c.nx : chunk_planes(CHUNK_BLOCKS_F16);
+  chunk(in, h->int_planes, &in_heavy, h->int_off);
   h->chunk_planes = planes;
   hipError_t err;
   for (int k = 0; k < 2; ++k) {

@@ -170,10 +170,11 @@ struct lbm_ctx {
   int* d_blist_bnd = nullptr;
   int n_int = 0, n_bnd = 0, cap_int = 0, cap_bnd = 0;
   // Offsets of the x-chunks of d_blist_bnd (chunks + 1 entries; one chunk
-  // except with FP32 storage on large lattices), and the x-planes per chunk.
-  std::vector<int> bnd_off;
-  std::vector<int> int_off;  // the same of d_blist_int
-  int chunk_planes = 0;
+  // except with FP32 storage on large lattices) and of d_blist_int (one except
+  // with FP16 storage on lattices beyond the fused kernel's), and the x-planes
+  // per chunk.
+  std::vector<int> bnd_off, int_off;
+  int chunk_planes = 0, int_planes = 0;
   int64_t int_nodes = 0;  // nodes updated by one bulk launch
   // FP16 storage: boundary blocks in the general kernel, then the bulk blocks
   // in a lean kernel; on lattices up to FUSED_MAX_NODES both in one fused

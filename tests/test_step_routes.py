@@ -98,3 +98,29 @@ def test_adjoint_pulls_the_state_non_temporally_where_sweeps_gain(storage, nz, m
     for ref in (False, True)[:1 + storage]:
         (_, _, _, targs), = double(ADJOINT % ((shape, storage, ref),), tmp_path)
         assert targs == [storage, int(ref), nt]
+
+
+DISPATCHES = """
+R = Runtime()
+A, L = R.A, R.L
+shape, kw, reference = %r
+h = R.channel(*shape, **kw)
+if reference:
+    assert L.lbm_set_reference(h, R.plane(9)) == A.LBM_OK
+R.launches.clear()
+d, p = C.c_int32(-1), C.c_int32(-1)
+assert L.lbm_timed_dispatches(None, C.byref(d), C.byref(p)) == A.LBM_ERR_ARG and d.value == p.value == -1
+assert L.lbm_timed_dispatches(h, C.byref(d), None) == L.lbm_timed_dispatches(h, None, C.byref(p)) == A.LBM_OK
+assert L.lbm_step(h, None, 1) == A.LBM_OK
+emit([[d.value, p.value], len([k for k, *_ in R.launches if k in ("collide_bulk_kernel", "collide_fused_kernel")]),
+      len([k for k, *_ in R.launches if k in ("collide_general_kernel", "collide_rows_kernel")])])
+"""
+
+
+@pytest.mark.parametrize("shape,storage,reference,dispatches", [
+    ((1536, 128, 384), 0, False, (10, 154)), ((64, 32, 32), 0, False, (1, 64)),
+    ((1536, 128, 384), 1, False, (5, 308)), ((1536, 256, 384), 1, False, (10, 154)),
+    ((1536, 128, 384), 1, True, (1, 1536)), ((768, 64, 192), 1, False, (1, 768)), ((64, 32, 32), 1, True, (1, 64))])
+def test_reported_dispatches_are_those_of_a_step(shape, storage, reference, dispatches, tmp_path):
+    got, bulk, other = double(DISPATCHES % ((shape, dict(storage=storage), reference),), tmp_path)
+    assert tuple(got) == dispatches and (bulk if storage else other) == dispatches[0]
