@@ -1,9 +1,11 @@
 """Gradients of plane-statistics losses by the library's discrete adjoint step.
 
 The forward run keeps the states and inlet planes of its last steps, as many
-as KEEP_SHARE of the free device memory holds (lbm_step_keep), and before them,
-or with `segment` given throughout, the state every `segment` steps (default
-about sqrt(T)).  The backward sweep runs lbm_adjoint_step backwards through the
+as KEEP_SHARE of the device memory that the run would leave free without them
+holds (lbm_step_keep), and before them, or with `segment` given throughout, the
+state every `segment` steps (default about sqrt(T)).  So a run takes memory in
+proportion to sqrt(T) with `segment` given, and up to KEEP_SHARE of the free
+memory more without, from its first forward run on for as long as it lives.  The backward sweep runs lbm_adjoint_step backwards through the
 kept states and recomputes each segment from its checkpoint into a ring of
 state buffers (lbm_step_record, which also keeps each step's inlet plane).
 Every step of both sweeps runs in the library's kernels; this module only
@@ -20,9 +22,10 @@ import numpy as np
 import torch
 
 
-# Share of the device memory free at the first forward run that the kept states
-# may take.  A kept step saves its recompute: 256 x 64 x 64, 30 steps, forward
-# and sweep 3.61 -> 2.68 ms.  The rest stays for the program.
+# Share of the device memory free at the first forward run, less what the run
+# takes besides, that the kept states may take.  A kept step saves its recompute:
+# 256 x 64 x 64, 30 steps, forward and sweep 3.61 -> 2.68 ms.  The rest stays for
+# the program.
 KEEP_SHARE = 1 / 8
 
 
@@ -49,10 +52,13 @@ class StatsGradient:
         self._ring = self._lam = self._kept = None
 
     def _keep_states(self):
-        """Number of states that fit KEEP_SHARE of the free device memory."""
+        """Number of states that fit KEEP_SHARE of the device memory that is free beside the
+        checkpoints, the recompute ring and the adjoint fields of a run without kept states."""
         dev = self.f0.device
         free = torch.cuda.mem_get_info(dev)[0] + torch.cuda.memory_reserved(dev) - torch.cuda.memory_allocated(dev)
-        return int(KEEP_SHARE * free) // (self.f0.nbytes + self.h0.nbytes + 6 * 4 * self.ch.ny * self.ch.nz)
+        state = self.f0.nbytes + self.h0.nbytes + 6 * 4 * self.ch.ny * self.ch.nz
+        need = (-(-self.T // self.seg) + max(self.seg - 1, 1)) * state + 2 * (4 * self.f0.numel() + self.h0.nbytes)
+        return max(0, int(KEEP_SHARE * (free - need)) // state)
 
     def _keep(self):
         """Buffers of the kept steps: n states and n + 1 inlet planes (of no step: n = 0)."""
