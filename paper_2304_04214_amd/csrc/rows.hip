@@ -250,10 +250,11 @@ __global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int r
 // take many turns and the launch is short enough to wait for them, sampled steps
 // go to the general kernel.  us per two steps with four planes, general -> this
 // one, by turns (twice as many with 32 lanes) and blocks of the general kernel:
-// 8 turns 41x60x2 (615) 22.7 -> 29.0, 206x60x2 (3090) 36.2 -> 40.0, 308x60x2 (4620)
+// 8 turns 41x60x2 (615) 22.7 -> 29.0, 240x60x2 (3600) 38.9 -> 41.3, 308x60x2 (4620)
 // 44.7 -> 42.4; 3 turns 41x20x4 (205) 19.7 -> 20.2; 4 turns 41x60x4 (615) 22.5 ->
-// 22.2, 41x60x24 (615) 21.7 -> 22.1, 103x60x24 (1545) 30.1 -> 27.4; 2 turns 41x20x12
-// (205) 19.5 -> 18.8.
+// 22.2, 41x60x24 (615) 21.7 -> 22.1, 103x60x24 (1545) 30.1 -> 27.4; 2 turns 21x20x8
+// (105) 18.9 -> 19.2, 41x20x8 (205) 19.3 -> 18.7; one turn of 32 lanes 21x20x28
+// (105) 19.2 -> 18.2.
 void plan_rows(lbm_ctx* h) {
   const lbm_config& c = h->cfg;
   h->rows = 0;
@@ -272,8 +273,8 @@ void plan_rows(lbm_ctx* h) {
   }
   if (!h->rows) return;
   const int per = c.nz <= 16 ? 4 : 2, at_once = h->row_threads / ZT * per;
-  const int turns = (h->rows + at_once - 1) / at_once * (4 / per);
-  h->rows_lose_sampled = (int64_t)c.nx * h->yg < 600 * (int64_t)(turns - 2);
+  const int turns = (h->rows + at_once - 1) / at_once;
+  h->rows_lose_sampled = turns > 1 && (int64_t)c.nx * h->yg < 128 + 700 * (int64_t)(turns * (4 / per) - 2);
 }
 
 // One dispatch, as the general kernel's of lattices this small.  The caller reads the
