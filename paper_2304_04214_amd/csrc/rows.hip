@@ -233,9 +233,20 @@ __global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int r
 
 }  // namespace
 
+// Touched bytes up to which the row kernel is taken: us per five steps, general
+// kernel -> this one, 1028x60x16 (300 MB) 260 -> 210, 617x100x24 289 -> 274, 617x100x32
+// 277 -> 251; rows that are no multiple of 32 bytes lose near the Infinity Cache's
+// size, 3084x20x17 (300 MB) 283 -> 298, 2878x20x17 (280 MB) 267 -> 275, 1028x60x3 257 ->
+// 267, 545x100x17 (265 MB) 258 -> 245, and earlier the longest of them, 617x100x28 289 ->
+// 306, 524x100x28 (255 MB) 249 -> 254, 442x100x28 (215 MB) 215 -> 206.
+int64_t rows_max(const lbm_config& c) {
+  const int mib = c.nz % 8 == 0 ? 288 : (c.nz <= 24 ? 264 : 224);
+  return (int64_t)mib << 20;
+}
+
 // Rows per block and blocks per plane of the row kernel (0 rows: not used).
 // FP32 storage with nz <= 32, where a step's stores stay in the caches for the
-// next (NT_STORE_MIN_BYTES): us per step, general kernel -> this one, 625x96x24
+// next (rows_max): us per step, general kernel -> this one, 625x96x24
 // (60,000 rows) 58.5 -> 48.3, 687x104x28 (71,000) 65 -> 108, with non-temporal
 // stores 82.  Beyond 32 a row leaves less than half the wave idle and little is
 // won by more nodes a wave (190x63x48 18.3 -> 18.4, 400x75x40 42.5 -> 46.5).
@@ -258,7 +269,7 @@ __global__ __launch_bounds__(MAXT) void collide_rows_kernel(CollideArgs a, int r
 void plan_rows(lbm_ctx* h) {
   const lbm_config& c = h->cfg;
   h->rows = 0;
-  if (c.storage != LBM_STORE_F32 || c.nz > MAXZ || touched_bytes(c) > NT_STORE_MIN_BYTES) return;
+  if (c.storage != LBM_STORE_F32 || c.nz > MAXZ || touched_bytes(c) > rows_max(c)) return;
   const bool small = h->N <= (int64_t(1) << 17);
   const int most = std::min((small ? MAXT / 2 : MAXT) / c.nz, c.ny);
   int64_t least = 0;  // threads of a plane

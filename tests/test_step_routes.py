@@ -51,6 +51,13 @@ def test_short_rows_within_the_caches_only(nz, mb, lanes, tmp_path):
         assert name == "collide_fused_kernel" and threads == 4 * lanes and targs[-1] == lanes
 
 
+@pytest.mark.parametrize("nz,mb,rows", [(16, 300, 1), (16, 305, 0), (32, 300, 1), (24, 300, 1), (17, 275, 1),
+                                        (17, 280, 0), (3, 300, 0), (28, 230, 1), (28, 240, 0), (33, 60, 0)])
+def test_row_kernel_within_the_infinity_cache_only(nz, mb, rows, tmp_path):
+    (name, *_), = step(tmp_path, lattice(nz, mb, 0, ny=60))
+    assert name == ("collide_rows_kernel" if rows else "collide_general_kernel")
+
+
 @pytest.mark.parametrize("storage,nz,mb,nt", [
     # FP32: 288 MiB (302 MB) with whole lines, 268 MiB (281 MB) with a part of one
     (0, 64, 300, 0), (0, 64, 305, 1), (0, 96, 300, 0), (0, 112, 278, 0), (0, 112, 284, 1), (0, 100, 284, 1),
