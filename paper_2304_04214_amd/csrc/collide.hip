@@ -913,11 +913,14 @@ hipError_t build_block_lists(lbm_ctx* h, const std::vector<int>& plane_of_x) {
   // 768x64x192 242 -> 239).  The sampled planes' too where the launch is little
   // more than one round of blocks (64x64x64 10.9 -> 9.9 us); on larger lattices
   // they are no tail, and many of them out of turn cost (128x96x336 with twelve,
-  // 112 -> 114.5).  FP16's general blocks run before the bulk blocks in any case
+  // 112 -> 114.5).  Few blocks go first only where a plane's columns fill the XCDs
+  // evenly (four steps with four planes, 41x64x64 44.1 -> 38.3 us, 20x30x128 36.8 ->
+  // 33.8): otherwise they cost (41x22x64 34.3 -> 36.4, 30x22x100 31.2 -> 33.0,
+  // 41x50x40 32.8 -> 34.8, 100x22x64 38.0 -> 39.2; 55x22x100, 660 blocks, 40.6 -> 38.0).  FP16's general blocks run before the bulk blocks in any case
   // and keep the order of x (64x64x64 10.4 us, outlet first 11.0).
   auto first_the_longest = [&](std::vector<int>& v) {
     const bool open = c.xbc == LBM_X_INFLOW;
-    const bool one_round = v.size() <= 2048;
+    const bool one_round = v.size() <= 2048 && (v.size() > 640 || h->yg % 8 == 0);
     std::vector<int> part[4];
     for (int e : v) {
       const int x = e / per_plane;

@@ -132,3 +132,31 @@ emit([[d.value, p.value], len([k for k, *_ in R.launches if k in ("collide_bulk_
 def test_reported_dispatches_are_those_of_a_step(shape, storage, reference, dispatches, tmp_path):
     got, bulk, other = double(DISPATCHES % ((shape, dict(storage=storage), reference),), tmp_path)
     assert tuple(got) == dispatches and (bulk if storage else other) == dispatches[0]
+
+
+ORDER = """
+R = Runtime()
+A, L = R.A, R.L
+shape, planes = %r
+h = R.channel(*shape)
+arr = (C.c_int32 * len(planes))(*planes)
+assert L.lbm_stats(h, A.STATS_ATTACH, arr, len(planes), None, None) == A.LBM_OK
+lists = []
+R.on_launch = lambda kernel, args: lists.append(C.cast(args[1], C.POINTER(C.c_void_p))[0])
+assert L.lbm_step(h, None, 1) == A.LBM_OK
+n = R.launches[0][1][0]
+per_plane = -(-shape[1] // 4) * -(-shape[2] // 64)
+xs = [e // per_plane for e in (C.c_int32 * n).from_address(lists[0]) if e >= 0]
+emit([R.launches[0][0], xs])
+"""
+
+
+@pytest.mark.parametrize("shape,first", [((41, 64, 64), 1), ((20, 30, 128), 1), ((41, 22, 64), 0), ((30, 22, 100), 0),
+                                         ((55, 22, 100), 1), ((100, 22, 64), 0), ((220, 40, 64), 0)])
+def test_sampled_planes_first_where_they_would_be_the_tail(shape, first, tmp_path):
+    planes = [7, 12]
+    kernel, xs = double(ORDER % ((shape, planes),), tmp_path)
+    blocks = -(-shape[1] // 4) * -(-shape[2] // 64)
+    assert kernel == "collide_general_kernel"
+    assert sorted(xs) == sorted(list(range(shape[0])) * blocks)
+    assert (set(xs[:8]) <= set(planes)) == bool(first)  # one of each XCD
