@@ -261,9 +261,11 @@ int64_t rows_max(const lbm_config& c) {
 // take several turns and the launch is short enough to wait for them, sampled steps
 // go to the general kernel.  us per two steps, general -> this one, by turns (twice
 // as many with 32 lanes) and blocks of the general kernel, two planes: 2 turns
-// 24x50x8 (312) 13.9 -> 14.2, 41x50x12 (533) 14.2 -> 15.4, 70x50x8 (910) 16.6 -> 15.5;
+// 24x50x8 (312) 13.9 -> 14.2, 41x50x12 (533) 14.2 -> 15.4, 168x16x5 (672, six steps,
+// eight planes) 43.0 -> 49.2, 70x50x8 (910) 16.6 -> 15.5;
 // 3 turns 41x50x6 (533) 14.1 -> 16.8, 70x50x6 (910) 16.5 -> 17.3, 120x50x6 (1560) 19.7 ->
-// 19.3; 4 turns 41x50x24 (533) 14.8 -> 17.4; four planes: 103x60x24 (1545) 30.1 -> 27.4;
+// 19.3; 4 turns 41x50x24 (533) 14.8 -> 17.4, 89x64x3 (1424) 18.5 -> 20.9; four
+// planes: 103x60x24 (1545) 30.1 -> 27.4;
 // 8 turns 41x60x2 (615) 22.7 -> 29.0, 240x60x2 (3600) 38.9 -> 41.3, 308x60x2 (4620)
 // 44.7 -> 42.4; one turn 16x50x16 13.8 -> 13.3, 21x20x28 19.2 -> 18.2.
 void plan_rows(lbm_ctx* h) {
@@ -286,7 +288,7 @@ void plan_rows(lbm_ctx* h) {
   const int per = c.nz <= 16 ? 4 : 2, at_once = h->row_threads / ZT * per;
   const int turns = (h->rows + at_once - 1) / at_once;
   const int64_t w = turns * (4 / per);
-  h->rows_lose_sampled = turns > 1 && (int64_t)c.nx * h->yg < 400 + 60 * w * w;
+  h->rows_lose_sampled = turns > 1 && (int64_t)c.nx * h->yg < 560 + 60 * w * w;
 }
 
 // One dispatch, as the general kernel's of lattices this small.  The caller reads the

@@ -76,7 +76,8 @@ def test_cached_stores_within_the_infinity_cache_only(storage, nz, mb, nt, tmp_p
 @pytest.mark.parametrize("shape,sampled", [
     ((41, 60, 2), "general"), ((240, 60, 2), "general"), ((308, 60, 2), "rows"), ((41, 20, 1), "general"),
     ((41, 20, 4), "general"), ((120, 60, 4), "rows"), ((41, 60, 24), "general"), ((103, 60, 24), "rows"),
-    ((41, 50, 12), "general"), ((70, 50, 8), "rows"), ((70, 50, 6), "general"), ((120, 50, 6), "rows"), ((16, 20, 16), "rows"), ((16, 20, 28), "rows"),
+    ((41, 50, 12), "general"), ((168, 16, 5), "general"), ((70, 50, 8), "rows"), ((70, 50, 6), "general"),
+    ((89, 64, 3), "general"), ((120, 50, 6), "rows"), ((16, 20, 16), "rows"), ((16, 20, 28), "rows"),
     ((16, 20, 32), "rows"), ((200, 20, 16), "rows")])
 def test_sampled_steps_leave_the_row_kernel_where_its_sums_take_longer(shape, sampled, tmp_path):
     assert [k for k, *_ in step(tmp_path, shape)] == ["collide_rows_kernel"]
