@@ -256,6 +256,13 @@ int64_t rows_max(const lbm_config& c) {
 // of which a quarter idles); above, the largest of up to 256 threads (400x40x32
 // 15.3 us, 16.9 with 128).  Every block has at least two rows, a wall row and the
 // row next to it.
+// A closed channel of up to one general block a CU keeps the general kernel with
+// the wall model, whose Newton steps and plain rows then share a wave here: us per
+// four steps, general -> this one, 13x10x6 20.4 -> 22.0, 13x60x14 20.7 -> 23.0, 40x24x6
+// (240 blocks) 20.9 -> 21.9, 24x60x8 (360) -> 1.09x; with one or two spanwise nodes, 64
+// rows a wave, up to 640: 13x60x2 20.7 -> 24.6, without walls 17.7 -> 19.6, 40x60x1
+// 25.9 -> 27.2.  In an open channel the end planes are the longest and their loads go
+// out earlier here: 1.00x to 1.29x from 24 blocks on.
 // A wave sums a sampled plane's rows a few at a time (four of up to 16 lanes, two
 // of 32, at twice the adds), the general kernel one each: where a block's rows
 // take several turns and the launch is short enough to wait for them, sampled steps
@@ -272,6 +279,7 @@ void plan_rows(lbm_ctx* h) {
   const lbm_config& c = h->cfg;
   h->rows = 0;
   if (c.storage != LBM_STORE_F32 || c.nz > MAXZ || touched_bytes(c) > rows_max(c)) return;
+  if (c.xbc != LBM_X_INFLOW && (int64_t)c.nx * h->yg <= (c.nz <= 2 ? 640 : (c.wall_model ? 256 : 0))) return;
   const bool small = h->N <= (int64_t(1) << 17);
   const int most = std::min((small ? MAXT / 2 : MAXT) / c.nz, c.ny);
   int64_t least = 0;  // threads of a plane

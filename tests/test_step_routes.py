@@ -73,6 +73,14 @@ def test_cached_stores_within_the_infinity_cache_only(storage, nz, mb, nt, tmp_p
     assert first[3][template] == nt and last[3][template] == 1
 
 
+@pytest.mark.parametrize("shape,kw,rows", [
+    ((40, 24, 6), dict(wall_model=1), 0), ((24, 60, 8), dict(wall_model=1), 1), ((13, 60, 32), dict(wall_model=1), 0),
+    ((40, 24, 6), dict(), 1), ((13, 60, 2), dict(), 0), ((40, 60, 1), dict(), 0), ((60, 60, 1), dict(), 1),
+    ((40, 24, 6), dict(wall_model=1, xbc=1), 1), ((13, 60, 2), dict(xbc=1), 1), ((5, 9, 16), dict(xbc=1), 1)])
+def test_small_closed_channels_keep_the_general_kernel(shape, kw, rows, tmp_path):
+    assert [k for k, *_ in step(tmp_path, shape, **kw)] == ["collide_rows_kernel" if rows else "collide_general_kernel"]
+
+
 @pytest.mark.parametrize("shape,sampled", [
     ((41, 60, 2), "general"), ((240, 60, 2), "general"), ((308, 60, 2), "rows"), ((41, 20, 1), "general"),
     ((41, 20, 4), "general"), ((120, 60, 4), "rows"), ((41, 60, 24), "general"), ((103, 60, 24), "rows"),
@@ -80,8 +88,8 @@ def test_cached_stores_within_the_infinity_cache_only(storage, nz, mb, nt, tmp_p
     ((89, 64, 3), "general"), ((120, 50, 6), "rows"), ((16, 20, 16), "rows"), ((16, 20, 28), "rows"),
     ((16, 20, 32), "rows"), ((200, 20, 16), "rows")])
 def test_sampled_steps_leave_the_row_kernel_where_its_sums_take_longer(shape, sampled, tmp_path):
-    assert [k for k, *_ in step(tmp_path, shape)] == ["collide_rows_kernel"]
-    assert [k for k, *_ in step(tmp_path, shape, planes=[1, 3])] == ["collide_%s_kernel" % sampled]
+    assert [k for k, *_ in step(tmp_path, shape, xbc=1)] == ["collide_rows_kernel"]
+    assert [k for k, *_ in step(tmp_path, shape, planes=[1, 3], xbc=1)] == ["collide_%s_kernel" % sampled]
 
 
 ADJOINT = """
