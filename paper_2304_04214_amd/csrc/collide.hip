@@ -433,8 +433,7 @@ constexpr int FUSED_SHORT_WAVES = 6;
 // give a row 32 (16) lanes, so that a wave holds two (four) rows of the block's
 // four and fewer lanes are without a node.  us per step with 64 lanes -> with these:
 // 400x40x32 24.1 -> 20.6, 64x32x32 9.9 -> 7.6, 600x60x24 32.2 -> 28.7,
-// 200x20x16 13.4 -> 10.3, 880x80x16 56.0 -> 55.1 (bound by the padded bricks'
-// 128-byte lines).
+// 200x20x16 13.4 -> 10.3.
 template <bool FORCE, bool REF, bool NT, int ZL>
 __global__ __launch_bounds__(YROWS* ZL) __attribute__((amdgpu_waves_per_eu(ZL == ZT ? 8 : FUSED_SHORT_WAVES)))
 void collide_fused_kernel(CollideArgs a, const int* __restrict__ gl, int n_gen, const int* __restrict__ bl,

@@ -32,8 +32,8 @@ constexpr int CHUNK_BLOCKS = 30000;
 // dispatches of about this many.  A gain of about 1% and fewer slow calls, us per
 // four steps with one dispatch -> with these: 1536x192x384 5793 -> 5689,
 // 1536x256x384 7606 -> 7548, 3072x64x384 3981 -> 3933, 1101x120x261 2213 -> 2138,
-// 1536x128x384 3824 -> 3833 (on other boxes 980 -> 934 to 953 a step; 64 planes a
-// dispatch 1032).  With reference offsets every range loses (1536x256x384 7891 ->
+// 1536x128x384 3824 -> 3833 (on other MI355Xs 980 -> 934 to 953 a step; 64 planes
+// a dispatch 1032).  With reference offsets every range loses (1536x256x384 7891 ->
 // 8014, 1536x192x384 5983 -> 6038, 1101x120x261 2207 -> 2230, 1536x128x384 4035 ->
 // 4069) and the step keeps one dispatch.
 constexpr int CHUNK_BLOCKS_F16 = 60000;
