@@ -78,7 +78,8 @@ __device__ __forceinline__ void x_rules(const CollideArgs& a, int x, int y, int 
 }
 
 // NT: non-temporal population stores (see CollideArgs::nt_store).
-template <bool F16, bool NT = true, int ZL = ZT>
+// LATE: the storage offsets are loaded with their stores, not ahead of them.
+template <bool F16, bool NT = true, int ZL = ZT, bool LATE = true>
 __device__ __forceinline__ void node_update(const CollideArgs& a, int x, int y, int z, int lane, int base, int zci,
                                             bool owned, bool active, const Col& col, float f[Q],
                                             float (*lds_u2)[2][ZL]) {
@@ -145,15 +146,16 @@ __device__ __forceinline__ void node_update(const CollideArgs& a, int x, int y, 
 
   if (active && owned) {
     char* p = const_cast<char*>(row_ptr<F16>(a.dst, rowpart(a, x, y)));
-    // Short rows load the offsets before the first store: between stores each per-lane load would
-    // wait for its own.  64-lane rows load them with scalar loads; there all of them ahead cost (FP16
-    // with reference, twelve sampled planes, us per four steps 914x90x100 723 -> 737).
+    // The offsets are loaded before the first store: between stores each load would wait for its own
+    // (us per six steps 48x64x64 81.7 -> 77.0, 16x90x100 85.0 -> 80.3).  On lattices beyond the caches,
+    // where other waves fill that wait, 64-lane rows keep theirs with the stores (914x90x100, twelve
+    // sampled planes, four steps 723, ahead 737).
     float ref[Q];
 #pragma unroll
-    for (int i = 0; i < Q; ++i) ref[i] = F16 && ZL < ZT ? ref_off(a, i, y) : 0.f;
+    for (int i = 0; i < Q; ++i) ref[i] = F16 && !LATE ? ref_off(a, i, y) : 0.f;
 #pragma unroll
     for (int i = 0; i < Q; ++i)
-      Pop<F16>::template stp<NT>(p + i * ZT * Pop<F16>::ES, i, col.b0, f[i], ZL < ZT ? ref[i] : ref_off(a, i, y));
+      Pop<F16>::template stp<NT>(p + i * ZT * Pop<F16>::ES, i, col.b0, f[i], LATE ? ref_off(a, i, y) : ref[i]);
   }
 
   if (a.stats_on) {
@@ -434,7 +436,7 @@ constexpr int FUSED_SHORT_WAVES = 6;
 // four and fewer lanes are without a node.  us per step with 64 lanes -> with these:
 // 400x40x32 24.1 -> 20.6, 64x32x32 9.9 -> 7.6, 600x60x24 32.2 -> 28.7,
 // 200x20x16 13.4 -> 10.3.
-template <bool FORCE, bool REF, bool NT, int ZL>
+template <bool FORCE, bool REF, bool NT, int ZL, bool LATE = false>
 __global__ __launch_bounds__(YROWS* ZL) __attribute__((amdgpu_waves_per_eu(ZL == ZT ? 8 : FUSED_SHORT_WAVES)))
 void collide_fused_kernel(CollideArgs a, const int* __restrict__ gl, int n_gen, const int* __restrict__ bl,
                           const float* __restrict__ dref, const float* __restrict__ dpull) {
@@ -458,7 +460,7 @@ void collide_fused_kernel(CollideArgs a, const int* __restrict__ gl, int n_gen, 
     issue_pulls<true, ZL == ZT>(a, g, col, r);
     float f[Q];
     convert_pulls<true, ZL == ZT>(a, g, r, f);
-    node_update<true, NT, ZL>(a, x, y, z, lane, base, zci, owned, active, col, f, lds_u2);
+    node_update<true, NT, ZL, LATE>(a, x, y, z, lane, base, zci, owned, active, col, f, lds_u2);
     return;
   }
   const int e = bl[b - n_gen];
@@ -746,6 +748,8 @@ void launch_bulk_kernel(lbm_ctx* h, const CollideArgs& a, hipStream_t stream) {
         collide_fused_kernel<F, R, N, 16><<<nt, YROWS * 16, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
       else if (lanes == 32)
         collide_fused_kernel<F, R, N, 32><<<nt, YROWS * 32, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
+      else if (R && N && touched_bytes(h->cfg) > nt_store_min(h->cfg))
+        collide_fused_kernel<F, R, N, ZT, R && N><<<nt, BLOCK, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
       else
         collide_fused_kernel<F, R, N, ZT><<<nt, BLOCK, 0, stream>>>(a, gl, ng, bl, a.dref, a.dpull);
     };

@@ -48,7 +48,7 @@ def lattice(nz, mb, storage, ny=90):
 def test_short_rows_within_the_caches_only(nz, mb, lanes, tmp_path):
     for ref in (False, True):
         (name, grid, threads, targs), = step(tmp_path, lattice(nz, mb, 1), reference=ref, storage=1)
-        assert name == "collide_fused_kernel" and threads == 4 * lanes and targs[-1] == lanes
+        assert name == "collide_fused_kernel" and threads == 4 * lanes and targs[3] == lanes
 
 
 @pytest.mark.parametrize("nz,mb,rows", [(16, 300, 1), (16, 305, 0), (32, 300, 1), (24, 300, 1), (17, 275, 1),
@@ -90,6 +90,14 @@ def test_small_closed_channels_keep_the_general_kernel(shape, kw, rows, tmp_path
 def test_sampled_steps_leave_the_row_kernel_where_its_sums_take_longer(shape, sampled, tmp_path):
     assert [k for k, *_ in step(tmp_path, shape, xbc=1)] == ["collide_rows_kernel"]
     assert [k for k, *_ in step(tmp_path, shape, planes=[1, 3], xbc=1)] == ["collide_%s_kernel" % sampled]
+
+
+@pytest.mark.parametrize("nz,mb,reference,late", [(64, 40, True, 0), (64, 200, True, 0), (64, 305, True, 1),
+                                                  (64, 305, False, 0), (80, 260, True, 1), (20, 330, True, 0),
+                                                  (20, 340, True, 1)])
+def test_storage_offsets_ahead_of_the_stores_within_the_caches(nz, mb, reference, late, tmp_path):
+    for _, _, _, targs in step(tmp_path, lattice(nz, mb, 1), reference=reference, steps=2, storage=1):
+        assert targs[4] == late
 
 
 ADJOINT = """
