@@ -216,7 +216,9 @@ __global__ __launch_bounds__(256) void stg_fill_kernel(lbm_stg s, StgTables t, i
 #pragma unroll
     for (int k = 0; k < RB; ++k) {
       const int y = min(y0 + k, ny - 1);
-      const double2 cs = cos_sin(ky * (y + 0.5) + ot * time + phi);
+      const double ph = ky * (y + 0.5) + ot * time + phi;
+      const double2 cs = cos_sin(ph);
+      if (k == 0 || k == RB - 1) far |= far_phase(ph);  // the rows between lie between
       rowph[k * N + n] = make_float2((float)cs.x, (float)cs.y);
       if (ROWAMP) {
         const float r = t.rowamp[(int64_t)y * N + n];
@@ -224,9 +226,8 @@ __global__ __launch_bounds__(256) void stg_fill_kernel(lbm_stg s, StgTables t, i
       }
     }
     if (!ROWAMP) amp[n] = make_float4(a0, a1, a2, 0.f);
-    far |= far_phase(fabs(ky) * ny + fabs(ot * time) + fabs(phi));  // no row's phase is larger
   }
-  if (far) {  // once more, apart: within the loop above it takes registers from the kernel
+  if (__builtin_expect(far, 0)) {  // once more, apart: within the loop above it takes registers from the kernel
 #pragma unroll 1
     for (int n = threadIdx.x; n < N; n += 256)
 #pragma unroll 1
