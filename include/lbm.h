@@ -251,11 +251,12 @@ lbm_status stg_inlet_fill_noalloc(lbm_handle h, const lbm_stg* stg, double t);
  * pull-stream / boundary / wall-model / MRT-Smagorinsky collision runs over
  * all nodes, on the handle's stream.  With LBM_STORE_F16DEV the blocks away
  * from the inlet, outlet and statistics planes (wall rows included) run in a
- * lean kernel, one dispatch per range of x-planes, after a general kernel for
- * the other blocks (one fused launch on lattices of up to 2^24 nodes); with
- * LBM_STORE_F32 the general kernel (on lattices of nz <= 32 that stay in the
- * caches the row kernel, with equal results) covers all blocks, one dispatch per
- * range of x-planes (lbm_collide_dispatches).
+ * lean kernel, without a storage reference one dispatch per range of x-planes
+ * (lbm_timed_dispatches), after a general kernel for the other blocks (one fused
+ * launch on lattices of up to 2^24 nodes); with LBM_STORE_F32 the general kernel
+ * covers all blocks, one dispatch per range of x-planes (lbm_collide_dispatches),
+ * or the row kernel, with equal results, on lattices of nz <= 32 that stay in the
+ * caches (but for the smallest closed ones, and small ones' sampled steps).
  * stg: bound when non-NULL; required (now or earlier) with LBM_X_INFLOW.
  * Asynchronous on the handle's stream.
  */
@@ -295,7 +296,8 @@ lbm_status lbm_set_reference(lbm_handle h, const double* u_ref);
  * u, v, w, uu, vv, ww, uv, uw, vw of the force-corrected velocity
  * (Eq. (11)) are accumulated in FP64 on the device during lbm_step.
  *   ATTACH  x_planes[n_planes] (distinct, in [0, nx)); allocates and zeroes
- *           the accumulators and starts accumulating.
+ *           the accumulators and starts accumulating.  LBM_ERR_HIP on a
+ *           stream under capture.
  *   DETACH  stop accumulating (accumulators kept).
  *   RESET   zero the accumulators and the sample count.
  *   READ    synchronise; host_out[n_planes][ny][9] = the means over z and the
